@@ -6,7 +6,8 @@ on every addition and multiplication being one IEEE round-to-nearest step.
 import os
 import shutil
 import subprocess
-import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -15,12 +16,12 @@ LIB = os.path.join(HERE, "libmdpe.so")
 ARCH = os.environ.get("MDPE_OFFLOAD_ARCH", "gfx950")
 
 HIPFLAGS = [
-    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
+    f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
     "-ffp-contract=off", "-fno-fast-math", "-fno-gpu-flush-denormals-to-zero",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-result",
 ]
-SOURCES = ["kernels.hip", "batch.hip", "plan.cpp"]
+SOURCES = ["kernels.hip", "addtree.hip", "batch.hip", "plan.cpp"]
 
 
 def hipcc() -> str:
@@ -30,9 +31,7 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def build(verbose: bool = False, extra=()) -> str:
-    cmd = [hipcc(), *HIPFLAGS, *extra, "-I", os.path.join(ROOT, "include"),
-           *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB + ".tmp"]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -42,6 +41,17 @@ def build(verbose: bool = False, extra=()) -> str:
         raise RuntimeError("hipcc failed:\n" + msg)
     if verbose and msg.strip():
         print(msg)
+
+
+def build(verbose: bool = False, extra=()) -> str:
+    """Compile every source (one hipcc each, side by side) and link the library."""
+    with tempfile.TemporaryDirectory(prefix="mdpe_build_") as tmp:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        base = [hipcc(), *HIPFLAGS, *extra, "-I", os.path.join(ROOT, "include")]
+        with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as pool:
+            list(pool.map(lambda so: _run([*base, "-c", os.path.join(CSRC, so[0]), "-o", so[1]], verbose),
+                          zip(SOURCES, objs)))
+        _run([hipcc(), f"--offload-arch={ARCH}", "-fPIC", "-shared", *objs, "-o", LIB + ".tmp"], verbose)
     os.replace(LIB + ".tmp", LIB)
     return LIB
 

@@ -45,17 +45,6 @@ namespace mdpe {
 
 // ------------------------------------------------------------------ kernels
 
-template <int M, bool CX>
-__global__ __launch_bounds__(256) void add_level_kernel(double *__restrict__ A, const int2 *__restrict__ pairs,
-                                                        long total, int d) {
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
-    const int d1 = d + 1;
-    const long p = idx / d1;
-    const int c = (int)(idx - p * d1);
-    add_item<M, CX>(A, pairs[p], c, d);
-}
-
 // A[dst] := e * A[src] at every coefficient of every scale job: one md_mul by
 // (e, 0, ..., 0) per part (general exponents, Section 3).
 template <int M, bool CX>
@@ -96,17 +85,6 @@ __global__ __launch_bounds__(256) void stage_kernel(double *__restrict__ A, cons
     const long e = idx / d1;
     const int c = (int)(idx - e * d1);
     stage_item(A, coeff, z, entries[e], c, N, n, d, m);
-}
-
-__global__ __launch_bounds__(256) void gather_kernel(const double *__restrict__ A, double *__restrict__ value,
-                                                     double *__restrict__ grad, const int *__restrict__ out_slots,
-                                                     int n, int d, int m) {
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    const int d1 = d + 1;
-    if (idx >= (long)(1 + n) * d1) return;
-    const int o = (int)(idx / d1);
-    const int c = (int)(idx - (long)o * d1);
-    gather_item(A, value, grad, out_slots[o], o, c, n, d, m);
 }
 
 // The whole evaluation in one launch of one workgroup, for plans so small
@@ -315,6 +293,8 @@ void free_plan(mdpe_plan *p) {
         (void)hipFree(p->d_pcodes);
         (void)hipFree(p->d_coff);
         (void)hipFree(p->d_aoff);
+        (void)hipFree(p->d_leaves);
+        (void)hipFree(p->d_chunks);
         (void)hipFree(p->d_schains);
     }
     delete p;
@@ -519,24 +499,6 @@ int launch_conv(const mdpe_plan *pl, double *A, hipStream_t st, mdpe_profiler *p
 }
 
 template <int M, bool CX>
-int launch_add(const mdpe_plan *pl, double *A, hipStream_t st, mdpe_profiler *prof) {
-    const mdpe::Plan &P = pl->P;
-    for (int r = 1; r <= P.n_levels(); ++r) {
-        const long off = P.add_off[r - 1];
-        const long np = P.add_off[r] - off;
-        if (np == 0) continue;
-        const long total = np * (P.d + 1);
-        int rc = record(prof, 2, st, true);
-        if (rc) return rc;
-        hipLaunchKernelGGL((mdpe::add_level_kernel<M, CX>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, A,
-                           pl->d_add + off, total, P.d);
-        LAUNCH_CHECK("add_level_kernel");
-        if ((rc = record(prof, 2, st, false))) return rc;
-    }
-    return MDPE_OK;
-}
-
-template <int M, bool CX>
 int launch_scale(const mdpe_plan *pl, double *A, hipStream_t st, mdpe_profiler *prof) {
     const mdpe::Plan &P = pl->P;
     if (P.scale.empty()) return MDPE_OK;
@@ -616,8 +578,7 @@ template <int M, bool CX>
 int run_field(const mdpe_plan *pl, double *A, hipStream_t st, mdpe_profiler *prof) {
     int rc;
     if ((rc = launch_conv<M, CX>(pl, A, st, prof))) return rc;
-    if ((rc = launch_scale<M, CX>(pl, A, st, prof))) return rc;
-    return launch_add<M, CX>(pl, A, st, prof);
+    return launch_scale<M, CX>(pl, A, st, prof);
 }
 
 template <int M>
@@ -670,13 +631,13 @@ int eval_impl(const mdpe_plan *pl, const double *coeff, const double *z, double 
         default: return fail(MDPE_EUNSUPPORTED, "unsupported m");
     }
     if (rc) return rc;
-    {
-        const long total = (long)(1 + P.n) * d1;
-        if ((rc = record(prof, 3, st, true))) return rc;
-        hipLaunchKernelGGL(mdpe::gather_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, A, value,
-                           grad, pl->d_out, P.n, P.d, P.w);
-        LAUNCH_CHECK("gather_kernel");
-        if ((rc = record(prof, 3, st, false))) return rc;
+    // the addition trees; the last pass writes value and gradient
+    const int passes = (int)pl->add_pass.size() - 1;
+    for (int p = 0; p < passes; ++p) {
+        const int cls = p + 1 < passes ? 2 : 3;
+        if ((rc = record(prof, cls, st, true)) || (rc = mdpe::launch_add_pass(pl, p, A, value, grad, st)) ||
+            (rc = record(prof, cls, st, false)))
+            return rc;
     }
     return MDPE_OK;
 }
@@ -823,6 +784,8 @@ int plan_polynomial(const mdpe_poly_desc *desc, int device, mdpe_plan **out) {
         std::vector<int2> add(P.add.size()), stage(P.stage.size());
         for (size_t q = 0; q < P.add.size(); ++q) add[q] = make_int2(P.add[q][0], P.add[q][1]);
         for (size_t q = 0; q < P.stage.size(); ++q) stage[q] = make_int2(P.stage[q][0], P.stage[q][1]);
+        const mdpe::AddPasses passes = mdpe::make_add_passes(P, mdpe::add_pass_cover(P.w));
+        pl->add_pass = passes.off;
         int rc;
         mdpe_plan *raw = pl.get();
         if ((rc = upload(&raw->d_conv, conv.data(), conv.size() * sizeof(int4))) ||
@@ -841,6 +804,8 @@ int plan_polynomial(const mdpe_poly_desc *desc, int device, mdpe_plan **out) {
             (rc = upload(&raw->d_pjobs, pjobs.data(), pjobs.size() * sizeof(int4))) ||
             (rc = upload(&raw->d_pcomps, P.pipe_comps.data(), P.pipe_comps.size() * sizeof(mdpe::ChainComp))) ||
             (rc = upload(&raw->d_pcodes, P.pipe_codes.data(), P.pipe_codes.size() * sizeof(int))) ||
+            (rc = upload(&raw->d_leaves, passes.leaves.data(), passes.leaves.size() * sizeof(int))) ||
+            (rc = upload(&raw->d_chunks, passes.chunks.data(), passes.chunks.size() * sizeof(mdpe::AddChunk))) ||
             (rc = upload(&raw->d_coff, coff.data(), coff.size() * sizeof(int))) ||
             (rc = upload(&raw->d_aoff, aoff.data(), aoff.size() * sizeof(int))) ||
             (rc = upload(&raw->d_schains, P.single_lanes.chains.data(), P.single_lanes.chains.size() * sizeof(int)))) {

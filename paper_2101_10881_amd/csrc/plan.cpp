@@ -165,6 +165,40 @@ static int tree_rounds(std::vector<int32_t> live, std::vector<std::vector<std::a
     return live.empty() ? -1 : live[0];
 }
 
+AddPasses make_add_passes(const Plan &P, int cover) {
+    AddPasses a;
+    a.off.push_back(0);
+    struct List {
+        int out;
+        std::vector<int32_t> slots;
+    };
+    std::vector<List> lists;
+    for (size_t o = 0; o + 1 < P.list_off.size(); ++o)
+        lists.push_back({(int)o, std::vector<int32_t>(P.list_slots.begin() + P.list_off[o],
+                                                      P.list_slots.begin() + P.list_off[o + 1])});
+    while (!lists.empty()) {
+        std::vector<List> left;
+        for (auto &L : lists) {
+            const int n = (int)L.slots.size(), base = (int)a.leaves.size();
+            a.leaves.insert(a.leaves.end(), L.slots.begin(), L.slots.end());
+            if (n <= cover) {
+                a.chunks.push_back({base, n, L.out, 0});
+                continue;
+            }
+            List up{L.out, {}};
+            for (int f = 0; f < n; f += cover) {
+                const int c = std::min(cover, n - f);
+                a.chunks.push_back({base + f, c, -1, 0});
+                up.slots.push_back(L.slots[f + c - 1]);
+            }
+            left.push_back(std::move(up));
+        }
+        a.off.push_back((int64_t)a.chunks.size());
+        lists.swap(left);
+    }
+    return a;
+}
+
 std::string check_hazards(const Plan &P) {
     // Each slot's last writer stage: inputs at stage 0, conv layer L at stage
     // L, addition level r at stage n_layers + r.  A job may read a slot only
@@ -1206,6 +1240,13 @@ static std::string build_plan_mode(int n, int N, int d, int m, const int32_t *nv
             P.conv_off.push_back((int64_t)P.conv.size());
         }
 
+    P.list_off.push_back(0);
+    auto keep_list = [&](const std::vector<int32_t> &l) {
+        P.list_slots.insert(P.list_slots.end(), l.begin(), l.end());
+        P.list_off.push_back((int64_t)P.list_slots.size());
+    };
+    keep_list(value_list);
+    for (int i = 0; i < n; ++i) keep_list(grad_lists[i]);
     std::vector<std::vector<std::array<int32_t, 2>>> rounds;
     P.out_slots.push_back(tree_rounds(value_list, rounds));
     for (int i = 0; i < n; ++i) P.out_slots.push_back(tree_rounds(grad_lists[i], rounds));

@@ -92,6 +92,10 @@ struct Plan {
     // coefficient, run after the last convolution layer, before the additions
     std::vector<std::array<int32_t, 3>> scale;
     LaneSchedule lanes;
+    // addition trees: the slots of each output's list (the value's, then each
+    // derivative's) in tree order; list o spans list_slots[list_off[o] .. list_off[o+1])
+    std::vector<int32_t> list_slots;
+    std::vector<int64_t> list_off;
     // reverse pass (flags & kKeepMonomialValues): one layer of correlation jobs
     // {t1 = ybar slot, t2 = M_k or gradient slot, t3 = output slot}
     int32_t ybar_slot = -1;
@@ -174,6 +178,24 @@ bool prefer_simple_dealing(int d, int J, int w, int schedule_steps);
 // turn (the slowest wavefront's).
 int dealt_steps(int d, int J, int Q = 1);
 int choose_jobs_per_group(int d, int w);
+// One workgroup's part of an addition pass: the leaves
+// leaves[first .. first+count) of one output's list.  out >= 0: the list's last
+// pass, the sum is output `out` (0 = value, 1+i = d/dz_i); else the sum goes to
+// the slot of the part's last leaf.
+struct AddChunk {
+    int32_t first, count, out, pad;
+};
+struct AddPasses {
+    std::vector<int32_t> leaves;
+    std::vector<AddChunk> chunks;
+    std::vector<int64_t> off;  // pass p spans chunks[off[p] .. off[p+1])
+};
+// The pairwise trees of every output list cut into passes of parts of at most
+// `cover` (a power of two) leaves: level r of a tree pairs whole runs of 2^r
+// leaves, so a part's own tree is a subtree, its result stands where the
+// level-by-level additions leave it, in its last leaf's slot, and the next
+// pass runs over those slots.
+AddPasses make_add_passes(const Plan &P, int cover);
 // The rules every plan meets (Section 5: the jobs of one layer are
 // independent): a job reads only slots written at an earlier stage (inputs,
 // an earlier layer or level); no two jobs of a stage write one slot, and no

@@ -7,6 +7,7 @@
 
 #include <atomic>
 #include <string>
+#include <vector>
 
 #include "plan.hpp"
 
@@ -34,8 +35,20 @@ struct mdpe_plan {
     int *d_pcodes = nullptr;   // chain launch: lane schedules
     int *d_coff = nullptr;     // single launch: convolution layer offsets (int32)
     int *d_aoff = nullptr;     // single launch: addition level offsets (int32)
+    int *d_leaves = nullptr;   // addition passes: list slots
+    mdpe::AddChunk *d_chunks = nullptr;  // addition passes: workgroups' parts
+    std::vector<int64_t> add_pass;       // pass p spans d_chunks[add_pass[p] .. add_pass[p+1])
     int *d_schains = nullptr;  // single launch: the lane schedule of its job groups
 };
+
+// launchers of the other translation units (each returns an MDPE_* status and
+// leaves its message for last_error_string)
+namespace mdpe {
+// Pass p of the plan's addition trees; the last pass of a list writes the
+// caller's value or gradient.
+int launch_add_pass(const mdpe_plan *pl, int p, double *A, double *value, double *grad, hipStream_t st);
+int add_pass_cover(int w);  // leaves of one workgroup's part
+}  // namespace mdpe
 
 namespace mdpe {
 void set_last_error(const std::string &msg);
