@@ -21,7 +21,7 @@ HIPFLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-result",
 ]
-SOURCES = ["kernels.hip", "addtree.hip", "batch.hip", "plan.cpp"]
+SOURCES = ["kernels.hip", "block.hip", "chain.hip", "addtree.hip", "batch.hip", "plan.cpp"]
 
 
 def hipcc() -> str:

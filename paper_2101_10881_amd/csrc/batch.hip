@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -37,6 +38,7 @@
 #include <vector>
 
 #include "../../include/mdpe.h"
+#include "conv_block.hpp"
 #include "conv_core.hpp"
 #include "plan.hpp"
 #include "runtime.hpp"
@@ -49,10 +51,13 @@ struct BatchInst {
     const double *z;
     double *value;
     double *grad;
-    const int4 *conv;
+    const int4 *conv;  // in launch order, or by set of components (goff)
+    const int *goff;   // component sets: group g spans conv[goff[g] .. goff[g + 1])
     const int2 *add;
+    const AddChunk *chunks;  // addition passes (blocked batches): parts of the output lists
+    const int *leaves;
     const int2 *stage;
-    const int *out;
+    const int *out;  // kSummed: written by an addition task
     const int *chains;
     int stride, steps, J;
     int simple;  // deal coefficients to lanes in turn (see conv_group)
@@ -65,41 +70,160 @@ struct BatchTask {
     int need;   // wait until the instance's completion counter reaches this
     int count;  // conv: jobs; others: items (coefficients)
     long first; // conv: first job; add: first (pair, coefficient) item; stage/gather: first item
+    // conv: a set of whole components, run group by group (groups > 0); add, by
+    // passes: `groups` (part, coefficient) items from item `group` (groups > 0)
+    int group, groups;
 };
 
 constexpr int kSpinLimit = 1 << 22;
 constexpr int kQueues = 8;  // one task queue per XCD
+constexpr int kSummed = -2;
+constexpr int kSetComponents = 512;  // resident wavefronts of an XCD (32 CUs x 16)
 
 // the XCD (XCC) this wavefront runs on
 __device__ __forceinline__ int xcd_id() { return (int)(__builtin_amdgcn_s_getreg(20 | (15 << 11)) & (kQueues - 1)); }
 
+// Terms an iteration of the blocked convolutions takes at width w.
+__host__ __device__ constexpr int batch_terms(int w) { return w <= 2 ? 4 : 2; }
+
+// An addition task by passes: each lane sums one part of an output's list (up to
+// add_pass_cover leaves) at one coefficient, E elements at a time with their
+// loads in flight together, in the pairs of the tree (an element's sum stands in
+// its last leaf's slot, as the level-by-level additions leave it; a lane reads
+// back only what it stored itself).  A launch stage per tree level cost a
+// release, an acquire and a memory latency per level and addition.
 template <int M>
+__device__ void add_parts(const BatchTask &T, const BatchInst &I, int lane) {
+    constexpr int E = M <= 4 ? 8 : 4;
+    const int d1 = I.d + 1;
+    const long S = (long)d1 * M;
+    for (int it = lane; it < T.groups; it += 64) {
+        const int q = T.group + it;
+        const int b = q / d1, c = q - b * d1;
+        const AddChunk ch = I.chunks[b];
+        if (ch.count < 2) continue;  // (one leaf or none: the gather's, or already in place)
+        const int *leaves = I.leaves + ch.first;
+        double *A = I.A + (long)c * M;
+        for (int len = ch.count, step = 1; len > 1; len = (len + E - 1) / E, step *= E) {
+            for (int r = 0; r < len; r += E) {
+                // element i's sum stands in the slot of leaf min((i + 1) * step, count) - 1
+                double v[E][M];
+                long off[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    off[e] = (long)leaves[min((min(r + e, len - 1) + 1) * step, ch.count) - 1] * S;
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+#pragma unroll
+                    for (int l = 0; l < M; ++l) v[e][l] = A[off[e] + l];
+#pragma unroll
+                for (int s = 1; s < E; s *= 2)
+#pragma unroll
+                    for (int p = 0; p < E; p += 2 * s)
+                        if (r + p + s < len) {
+                            double z[M];
+                            md_add<M>(v[p + s], v[p], z);
+#pragma unroll
+                            for (int l = 0; l < M; ++l) v[p][l] = z[l];
+                        }
+                if (len <= E && ch.out >= 0) {
+#pragma unroll
+                    for (int l = 0; l < M; ++l) {
+                        if (ch.out == 0)
+                            I.value[(long)l * d1 + c] = v[0][l];
+                        else
+                            I.grad[((long)l * I.n + (ch.out - 1)) * d1 + c] = v[0][l];
+                    }
+                } else {
+#pragma unroll
+                    for (int l = 0; l < M; ++l) A[off[E - 1] + l] = v[0][l];
+                }
+            }
+        }
+    }
+}
+
+template <int M, bool BLK>
 __device__ void run_task(const BatchTask &T, const BatchInst &I, double *lds, int lane) {
     const int d1 = I.d + 1;
     const int kind = __builtin_amdgcn_readfirstlane(T.kind);
     if (kind == 1) {
-        for (int g = 0; g < T.count; g += I.J) {
-            // chain codes loaded every step: 1.4% faster here (512 mixed
-            // instances) than at chain starts
-            conv_group<M, false, false, false, true>(I.A, I.conv + T.first + g, min(I.J, T.count - g), I.J, I.d, lds,
-                                                     I.chains, I.stride, I.steps, lane, lane, I.simple != 0);
-            __syncthreads();
+        if constexpr (BLK) {
+            // a set's groups one after the other (the barrier orders a group's
+            // stores before the next one's loads), or a run of one layer's jobs
+            const int groups = T.groups > 0 ? T.groups : (T.count + I.J - 1) / I.J;
+            for (int g = 0; g < groups; ++g) {
+                long a = T.first + (long)g * I.J;
+                int jn = min(I.J, T.count - g * I.J);
+                if (T.groups > 0) {
+                    a = I.goff[T.group + g];
+                    jn = I.goff[T.group + g + 1] - (int)a;
+                }
+                conv_block_group<M, false, false, 1, batch_terms(M)>(I.A, I.conv + a, __builtin_amdgcn_readfirstlane(jn),
+                                                                     I.J, I.d, lds, I.chains, I.stride, I.steps, lane,
+                                                                     lane);
+                __syncthreads();
+            }
+        } else {
+            for (int g = 0; g < T.count; g += I.J) {
+                // chain codes loaded every step: 1.4% faster here (512 mixed
+                // instances) than at chain starts
+                conv_group<M, false, false, false, true>(I.A, I.conv + T.first + g, min(I.J, T.count - g), I.J, I.d,
+                                                         lds, I.chains, I.stride, I.steps, lane, lane, I.simple != 0);
+                __syncthreads();
+            }
         }
     } else {
         // item T.first + q, q = lane, lane + 64, ...: series e, coefficient c.
         // One 64-bit division per lane and task; each iteration then adds
         // (64 / d1, 64 % d1) with a carry.
+        if (BLK && kind == 2 && T.groups > 0) {
+            add_parts<M>(T, I, lane);
+            return;
+        }
         const long f = T.first + lane;
         long e = f / d1;
         int c = (int)(f - e * d1);
         const int qe = 64 / d1, qc = 64 - qe * d1;
+        if (BLK && kind == 0) {
+            // four items' loads in flight per lane
+            for (int q = lane; q < T.count; q += 256) {
+                double v[4][M];
+                double *to[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (q + 64 * u < T.count) {
+                        const int2 en = I.stage[e];
+                        const bool co = en.y <= I.N;
+                        const double *src = co ? I.coeff + (long)en.y * d1 + c : I.z + (long)(en.y - I.N - 1) * d1 + c;
+                        const long plane = (long)(co ? I.N + 1 : I.n) * d1;
+#pragma unroll
+                        for (int l = 0; l < M; ++l) v[u][l] = src[l * plane];
+                        to[u] = I.A + ((long)en.x * d1 + c) * M;
+                    }
+                    e += qe;
+                    c += qc;
+                    if (c >= d1) {
+                        c -= d1;
+                        ++e;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (q + 64 * u < T.count) {
+#pragma unroll
+                        for (int l = 0; l < M; ++l) to[u][l] = v[u][l];
+                    }
+            }
+            return;
+        }
         for (int q = lane; q < T.count; q += 64) {
             if (kind == 0)
                 stage_item(I.A, I.coeff, I.z, I.stage[e], c, I.N, I.n, I.d, M);
             else if (kind == 2)
                 add_item<M>(I.A, I.add[e], c, I.d);
-            else
-                gather_item(I.A, I.value, I.grad, I.out[e], (int)e, c, I.n, I.d, M);
+            else if (const int slot = I.out[e]; slot != kSummed)
+                gather_item(I.A, I.value, I.grad, slot, (int)e, c, I.n, I.d, M);
             e += qe;
             c += qc;
             if (c >= d1) {
@@ -120,8 +244,9 @@ __global__ __launch_bounds__(64) void batch_reset_kernel(int *ctl, int n) {
 // Up to quad double the kernel asks for six resident wavefronts per SIMD
 // (at most 80 VGPRs, no spills), the occupancy its register use allowed
 // before the convolution loop kept operand addresses per lane.
-template <int M1, int M2>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(M2 <= 4 ? 6 : 1))) void batch_kernel(const BatchTask *__restrict__ tasks, const int *__restrict__ qinfo,
+// BLK: every instance's convolutions run by blocks (conv_block.hpp).
+template <int M1, int M2, bool BLK>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(BLK ? 4 : M2 <= 4 ? 6 : 1))) void batch_kernel(const BatchTask *__restrict__ tasks, const int *__restrict__ qinfo,
                                                    const BatchInst *__restrict__ insts, int *ctl) {
     extern __shared__ double lds[];
     const int lane = threadIdx.x;
@@ -161,9 +286,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(M2 <= 4 ? 6 
         }
         const BatchInst I = insts[inst];
         if (__builtin_amdgcn_readfirstlane(I.m) == M1)
-            run_task<M1>(T, I, lds, lane);
+            run_task<M1, BLK>(T, I, lds, lane);
         else
-            run_task<M2>(T, I, lds, lane);
+            run_task<M2, BLK>(T, I, lds, lane);
         // release: the fence waits for this wavefront's stores and writes the
         // L2 back; then lane 0 moves the instance's completion counter
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -203,10 +328,18 @@ struct mdpe_batch {
     std::vector<int> inst_queue; // queue of each instance, -1: dealt over all queues
     std::vector<int> task_queue; // queue of each task, in task order
     std::vector<int *> d_chains;
+    // instances run by component sets: their jobs set by set, layer by layer, and the groups
+    std::vector<std::vector<int4>> set_jobs;
+    std::vector<std::vector<int>> set_groups;
+    int4 *d_set_jobs = nullptr;
+    int *d_set_groups = nullptr;
+    std::vector<int> outs;  // blocked batches: every instance's output slots, kSummed where a list has additions
+    int *d_outs = nullptr;
     size_t lds = 0;
     int grid = 0;
     bool grid_fixed = false;
     int m1 = 0, m2 = 0;
+    bool blocks = false;  // convolutions by blocks
     bool buffers_set = false;
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
@@ -250,25 +383,28 @@ void free_batch(mdpe_batch *b) {
     (void)hipFree(b->d_qinfo);
     (void)hipFree(b->d_ctl);
     for (auto p : b->d_chains) (void)hipFree(p);
+    (void)hipFree(b->d_set_jobs);
+    (void)hipFree(b->d_set_groups);
+    (void)hipFree(b->d_outs);
     if (prev >= 0 && b->device >= 0) (void)hipSetDevice(prev);
     delete b;
 }
 
 // Kernel attributes and the persistent grid (resident one-wavefront
 // workgroups), resolved once, outside any stream capture.
-template <int M1, int M2>
+template <int M1, int M2, bool BLK>
 int prepare_batch(mdpe_batch *b) {
     // the LDS limit is a per-device function attribute: raise it once per device
     static std::atomic<bool> attr[kMaxDevices];
     const int dv = b->device >= 0 && b->device < kMaxDevices ? b->device : 0;
     if (b->lds > 65536 && !attr[dv].load()) {
-        BHIP(hipFuncSetAttribute((const void *)mdpe::batch_kernel<M1, M2>, hipFuncAttributeMaxDynamicSharedMemorySize,
+        BHIP(hipFuncSetAttribute((const void *)mdpe::batch_kernel<M1, M2, BLK>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                  (int)mdpe::kMaxLdsBytes));
         attr[dv].store(true);
     }
     if (b->grid == 0) {
         int per_cu = 0, cus = 0;
-        BHIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)mdpe::batch_kernel<M1, M2>, 64,
+        BHIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)mdpe::batch_kernel<M1, M2, BLK>, 64,
                                                           b->lds));
         BHIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device));
         // every XCD needs resident wavefronts to drain its queue; a CU's four
@@ -280,14 +416,14 @@ int prepare_batch(mdpe_batch *b) {
     return MDPE_OK;
 }
 
-template <int M1, int M2>
+template <int M1, int M2, bool BLK>
 int launch_batch(mdpe_batch *b, hipStream_t st, bool prepare_only) {
-    int rc = prepare_batch<M1, M2>(b);
+    int rc = prepare_batch<M1, M2, BLK>(b);
     if (rc || prepare_only) return rc;
     hipLaunchKernelGGL(mdpe::batch_reset_kernel, dim3(1), dim3(64), 0, st, b->d_ctl, b->count + mdpe::kQueues + 1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return bfail(MDPE_EDEVICE, std::string("batch_reset_kernel: ") + hipGetErrorString(e));
-    hipLaunchKernelGGL((mdpe::batch_kernel<M1, M2>), dim3(b->grid), dim3(64), b->lds, st, b->d_tasks, b->d_qinfo,
+    hipLaunchKernelGGL((mdpe::batch_kernel<M1, M2, BLK>), dim3(b->grid), dim3(64), b->lds, st, b->d_tasks, b->d_qinfo,
                        b->d_insts, b->d_ctl);
     e = hipGetLastError();
     if (e != hipSuccess) return bfail(MDPE_EDEVICE, std::string("batch_kernel: ") + hipGetErrorString(e));
@@ -296,14 +432,21 @@ int launch_batch(mdpe_batch *b, hipStream_t st, bool prepare_only) {
 
 int launch_any(mdpe_batch *b, hipStream_t st, bool prepare_only = false) {
 #define MS(a, c) (b->m1 == (a) && b->m2 == (c))
-    if (MS(1, 1)) return launch_batch<1, 1>(b, st, prepare_only);
-    if (MS(2, 2)) return launch_batch<2, 2>(b, st, prepare_only);
-    if (MS(3, 3)) return launch_batch<3, 3>(b, st, prepare_only);
-    if (MS(4, 4)) return launch_batch<4, 4>(b, st, prepare_only);
-    if (MS(5, 5)) return launch_batch<5, 5>(b, st, prepare_only);
-    if (MS(8, 8)) return launch_batch<8, 8>(b, st, prepare_only);
-    if (MS(10, 10)) return launch_batch<10, 10>(b, st, prepare_only);
-    if (MS(2, 4)) return launch_batch<2, 4>(b, st, prepare_only);
+    if (b->blocks) {
+        if (MS(2, 2)) return launch_batch<2, 2, true>(b, st, prepare_only);
+        if (MS(3, 3)) return launch_batch<3, 3, true>(b, st, prepare_only);
+        if (MS(4, 4)) return launch_batch<4, 4, true>(b, st, prepare_only);
+        if (MS(5, 5)) return launch_batch<5, 5, true>(b, st, prepare_only);
+        if (MS(2, 4)) return launch_batch<2, 4, true>(b, st, prepare_only);
+    }
+    if (MS(1, 1)) return launch_batch<1, 1, false>(b, st, prepare_only);
+    if (MS(2, 2)) return launch_batch<2, 2, false>(b, st, prepare_only);
+    if (MS(3, 3)) return launch_batch<3, 3, false>(b, st, prepare_only);
+    if (MS(4, 4)) return launch_batch<4, 4, false>(b, st, prepare_only);
+    if (MS(5, 5)) return launch_batch<5, 5, false>(b, st, prepare_only);
+    if (MS(8, 8)) return launch_batch<8, 8, false>(b, st, prepare_only);
+    if (MS(10, 10)) return launch_batch<10, 10, false>(b, st, prepare_only);
+    if (MS(2, 4)) return launch_batch<2, 4, false>(b, st, prepare_only);
 #undef MS
     return bfail(MDPE_EUNSUPPORTED, "batch precisions must be all equal, or {2, 4}");
 }
@@ -540,8 +683,20 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         if (t.jobs_per_group <= 0) t.jobs_per_group = mdpe::choose_jobs_per_group(d, m);
         return t;
     };
-    // schedules per (d, J)
-    std::map<std::pair<int, int>, int> sched_index;
+    // Convolutions by blocks at two to five doubles per coefficient, where
+    // every instance meets what the blocked kernel needs (32-bit offsets;
+    // second operands read from global memory not at the workspace's ends;
+    // a group's padded operands in LDS)
+    B->blocks = ms[0] >= 2 && ms.back() <= 5;
+    for (int p = 0; p < count && B->blocks; ++p) {
+        const mdpe::Plan &P = plans[p]->P;
+        B->blocks = mdpe::block_group_bytes(P.d + 1, P.m, mdpe::batch_terms(P.m), tile_for(P.m, P.d).jobs_per_group) <=
+                        mdpe::kMaxLdsBytes &&
+                    mdpe::small_workspace(P) &&
+                    (mdpe::stages_second_operand(P.m) || mdpe::reads_inside(P, P.conv, mdpe::batch_terms(P.m) - 1));
+    }
+    // schedules per (d, J, terms an iteration)
+    std::map<std::array<int, 3>, int> sched_index;
     std::vector<mdpe::LaneSchedule> scheds;
     // tasks with their depth and an instance cost for ordering
     struct Tmp {
@@ -582,6 +737,23 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         qload[best] += icost[p];
         B->inst_queue[p] = best;
     }
+    // Convolutions by component sets where a queue has a component for every
+    // resident wavefront of its XCD (32 CUs x 16): a task then runs whole
+    // components (monomials), its groups one after the other on one wavefront,
+    // and no convolution waits for another task -- one stage instead of a
+    // layer's after layer's, each with its release, acquire and idle
+    // wavefronts, and the longest tasks first.  Smaller batches keep a stage per
+    // layer: a component's products in sequence would be their critical path.
+    std::vector<std::vector<int32_t>> comp(count);
+    std::vector<int32_t> comps(count, 0);
+    std::vector<long> queue_comps(mdpe::kQueues, 0);
+    for (int p = 0; p < count && B->blocks; ++p) {
+        if (B->inst_queue[p] < 0) continue;
+        comps[p] = mdpe::job_components(plans[p]->P, comp[p]);
+        queue_comps[B->inst_queue[p]] += comps[p];
+    }
+    B->set_jobs.resize(count);
+    B->set_groups.resize(count);
     std::vector<Tmp> tmp;
     B->insts.resize(count);
     // one workspace for all instances: each instance's part 256-byte aligned
@@ -597,24 +769,29 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         const mdpe::Plan &P = plans[p]->P;
         const mdpe_batch_tile t = tile_for(P.m, P.d);
         const int J = t.jobs_per_group;
-        auto key = std::make_pair(P.d, J);
+        const std::array<int, 3> key{P.d, J, B->blocks ? mdpe::batch_terms(P.m) : 0};
         if (!sched_index.count(key)) {
             sched_index[key] = (int)scheds.size();
-            scheds.push_back(mdpe::make_lane_schedule(P.d, J));
+            scheds.push_back(B->blocks ? mdpe::make_block_schedule(P.d, 1, mdpe::batch_terms(P.m), J, 1)
+                                       : mdpe::make_lane_schedule(P.d, J));
         }
         const mdpe::LaneSchedule &S = scheds[sched_index[key]];
+        const int terms = S.steps * (B->blocks ? mdpe::batch_terms(P.m) : 1);
         // a dealt instance finds its parallelism inside its own layers: one
         // group of jobs per task, small addition tasks
         const bool dealt = B->inst_queue[p] < 0;
-        const int G = dealt ? 1 : t.groups_per_task > 0 ? t.groups_per_task : std::max(1, (256 + S.steps - 1) / S.steps);
+        const int G = dealt ? 1 : t.groups_per_task > 0 ? t.groups_per_task : std::max(1, (256 + terms - 1) / terms);
         const long items_per_task = dealt ? 1024 : t.add_items_per_task > 0 ? t.add_items_per_task : 4096;
-        lds = std::max(lds, (size_t)mdpe::group_lds_bytes(P.d + 1, mdpe::lds_doubles_per_coef(P.m), J));
+        lds = std::max(lds, (size_t)(B->blocks ? mdpe::block_group_bytes(P.d + 1, P.m, mdpe::batch_terms(P.m), J)
+                                               : mdpe::group_lds_bytes(P.d + 1, mdpe::lds_doubles_per_coef(P.m), J)));
         if (lds > (size_t)mdpe::kMaxLdsBytes)
             return bfail(MDPE_EUNSUPPORTED, "a tile's jobs_per_group needs more LDS than one workgroup has");
         mdpe::BatchInst &I = B->insts[p];
         std::memset(&I, 0, sizeof(I));
         I.conv = plans[p]->d_conv;
         I.add = plans[p]->d_add;
+        I.chunks = plans[p]->d_chunks;
+        I.leaves = plans[p]->d_leaves;
         I.stage = plans[p]->d_stage;
         I.out = plans[p]->d_out;
         I.stride = S.stride;
@@ -631,7 +808,7 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         int depth = 0, done_before = 0, order = 0;
         auto emit = [&](int kind, long first, int cnt, int need) {
             const int q = queue >= 0 ? queue : (p + order) % mdpe::kQueues;
-            tmp.push_back({q, depth, cost, order++, {p, kind, need, cnt, first}});
+            tmp.push_back({q, depth, cost, order++, {p, kind, need, cnt, first, 0, 0}});
         };
         auto items = [&](int kind, long total) {
             int n = 0;
@@ -642,13 +819,90 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         // stage
         done_before += items(0, (long)P.stage.size() * d1);
         ++depth;
-        for (int L = 1; L <= P.n_layers(); ++L, ++depth) {
+        const bool by_sets = !dealt && comps[p] > 0 && queue_comps[queue] >= mdpe::kSetComponents;
+        if (by_sets) {
+            // 2J components per set, so that a layer's jobs fill groups of J (a
+            // tile may ask for more work per task), but two sets per wavefront
+            // of the XCD
+            const double per_comp = (double)P.conv.size() / comps[p];
+            int cps = std::max(2 * J, (int)((double)t.groups_per_task * J / per_comp));
+            cps = (int)std::max(1L, std::min((long)cps, queue_comps[queue] / (2 * mdpe::kSetComponents)));
+            const int sets = (comps[p] + cps - 1) / cps, nl = P.n_layers();
+            // components of like size in one set (a set's layers then fill their
+            // groups: 0.97 to 0.99 of the places taken instead of 0.87 to 0.94)
+            {
+                std::vector<int32_t> size(comps[p], 0), rank(comps[p]), order(comps[p]);
+                for (int32_t c : comp[p]) ++size[c];
+                for (int32_t c = 0; c < comps[p]; ++c) order[c] = c;
+                std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t c) { return size[a] > size[c]; });
+                for (int32_t r = 0; r < comps[p]; ++r) rank[order[r]] = r;
+                for (int32_t &c : comp[p]) c = rank[c];
+            }
+            // counting sort by (set, layer)
+            std::vector<int> at((size_t)sets * nl + 1, 0);
+            for (int L = 1; L <= nl; ++L)
+                for (int64_t j = P.conv_off[L - 1]; j < P.conv_off[L]; ++j) at[(size_t)(comp[p][j] / cps) * nl + L]++;
+            for (size_t q = 1; q < at.size(); ++q) at[q] += at[q - 1];
+            std::vector<int> to(at.begin(), at.end() - 1);
+            auto &jobs = B->set_jobs[p];
+            jobs.resize(P.conv.size());
+            for (int L = 1; L <= nl; ++L)
+                for (int64_t j = P.conv_off[L - 1]; j < P.conv_off[L]; ++j)
+                    jobs[to[(size_t)(comp[p][j] / cps) * nl + L - 1]++] =
+                        make_int4(P.conv[j][0], P.conv[j][1], P.conv[j][2], 0);
+            auto &groups = B->set_groups[p];
+            for (int s = 0; s < sets; ++s) {
+                const int g0 = (int)groups.size(), first = at[(size_t)s * nl], last = at[(size_t)(s + 1) * nl];
+                for (int L = 0; L < nl; ++L)
+                    for (int j = at[(size_t)s * nl + L]; j < at[(size_t)s * nl + L + 1]; j += J) groups.push_back(j);
+                emit(1, first, last - first, done_before);
+                mdpe::BatchTask &T = tmp.back().t;
+                T.group = g0;
+                T.groups = (int)groups.size() - g0;
+                tmp.back().cost = T.groups * (double)S.steps * (mdpe::batch_terms(P.m) * P.m * P.m + 10.0);
+            }
+            groups.push_back((int)jobs.size());
+            done_before += sets;
+            ++depth;
+        }
+        for (int L = 1; !by_sets && L <= P.n_layers(); ++L, ++depth) {
             const long a = P.conv_off[L - 1], z = P.conv_off[L];
             int n = 0;
             for (long f = a; f < z; f += (long)G * J, ++n) emit(1, f, (int)std::min((long)G * J, z - f), done_before);
             done_before += n;
         }
-        for (int r = 1; r <= P.n_levels(); ++r, ++depth) {
+        // additions by passes over parts of the lists (plan's chunks), a task for
+        // about add_items_per_task additions of coefficients
+        const mdpe::AddPasses passes = B->blocks ? mdpe::make_add_passes(P, mdpe::add_pass_cover(P.w)) : mdpe::AddPasses();
+        const bool by_passes = B->blocks && (long)passes.chunks.size() * d1 < INT32_MAX;
+        if (by_passes) {
+            long done = 0;  // additions in the tasks so far: a task's `first` and `count` number them
+            for (size_t q = 0; q + 1 < passes.off.size(); ++q) {
+                const long lo = passes.off[q], hi = passes.off[q + 1];
+                long adds = 0;
+                for (long b = lo; b < hi; ++b) adds += std::max(0, passes.chunks[b].count - 1);
+                if (adds == 0) continue;
+                const long want = t.add_items_per_task > 0 ? t.add_items_per_task : 16384;
+                const long per = std::max(64L, std::min(65536L, want * (hi - lo) / adds / 64 * 64));
+                int n = 0;
+                for (long f = lo * d1; f < hi * d1; f += per, ++n) {
+                    const long e = std::min(f + per, hi * d1);
+                    long cnt = 0;
+                    for (long b = f / d1; b * d1 < e; ++b)
+                        cnt += (std::min(e, (b + 1) * d1) - std::max(f, b * d1)) * std::max(0, passes.chunks[b].count - 1);
+                    emit(2, done, (int)cnt, done_before);
+                    tmp.back().t.group = (int)f;
+                    tmp.back().t.groups = (int)(e - f);
+                    done += cnt;
+                }
+                done_before += n;
+                ++depth;
+            }
+        }
+        if (B->blocks)
+            for (size_t o = 0; o < P.out_slots.size(); ++o)
+                B->outs.push_back(by_passes && P.list_off[o + 1] - P.list_off[o] >= 2 ? mdpe::kSummed : P.out_slots[o]);
+        for (int r = 1; !by_passes && r <= P.n_levels(); ++r, ++depth) {
             const long a = P.add_off[r - 1] * d1, z = P.add_off[r] * d1;
             int n = 0;
             for (long f = a; f < z; f += items_per_task, ++n)
@@ -694,9 +948,31 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         B->d_chains.push_back(dc);
     }
     if (!rc) {
+        std::vector<int4> jobs;
+        std::vector<int> groups;
+        for (int p = 0; p < count; ++p) {
+            jobs.insert(jobs.end(), B->set_jobs[p].begin(), B->set_jobs[p].end());
+            groups.insert(groups.end(), B->set_groups[p].begin(), B->set_groups[p].end());
+        }
+        if (!jobs.empty() && !(rc = alloc_copy((void **)&B->d_set_jobs, jobs.data(), jobs.size() * sizeof(int4))))
+            rc = alloc_copy((void **)&B->d_set_groups, groups.data(), groups.size() * sizeof(int));
+    }
+    if (!rc && B->blocks) rc = alloc_copy((void **)&B->d_outs, B->outs.data(), B->outs.size() * sizeof(int));
+    if (!rc) {
+        size_t jobs_at = 0, groups_at = 0, outs_at = 0;
         for (int p = 0; p < count; ++p) {
             const mdpe::Plan &P = plans[p]->P;
-            B->insts[p].chains = B->d_chains[sched_index[{P.d, B->insts[p].J}]];
+            if (B->blocks) {
+                B->insts[p].out = B->d_outs + outs_at;
+                outs_at += P.out_slots.size();
+            }
+            if (!B->set_jobs[p].empty()) {
+                B->insts[p].conv = B->d_set_jobs + jobs_at;
+                B->insts[p].goff = B->d_set_groups + groups_at;
+                jobs_at += B->set_jobs[p].size();
+                groups_at += B->set_groups[p].size();
+            }
+            B->insts[p].chains = B->d_chains[sched_index[{P.d, B->insts[p].J, B->blocks ? mdpe::batch_terms(P.m) : 0}]];
         }
         if (!(rc = alloc_copy((void **)&B->d_tasks, B->tasks.data(), B->tasks.size() * sizeof(mdpe::BatchTask))) &&
             !(rc = alloc_copy((void **)&B->d_qinfo, B->qinfo.data(), B->qinfo.size() * sizeof(int))))

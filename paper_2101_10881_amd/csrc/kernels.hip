@@ -28,11 +28,13 @@
 //   gather_kernel        output slots -> user value / gradient (zeros if absent)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <memory>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/mdpe.h"
@@ -222,6 +224,18 @@ __global__ __launch_bounds__(256) void md_elementwise_kernel(int op, long count,
 // ------------------------------------------------------------------ runtime
 
 namespace mdpe {
+int simd_count(int device) {
+    static std::atomic<int> cached[kMaxDevices];
+    if (device < 0 || device >= kMaxDevices) return 1024;
+    if (!cached[device]) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
+            cus = 256;
+        cached[device] = 4 * cus;
+    }
+    return cached[device];
+}
+
 static thread_local std::string g_err;
 void set_last_error(const std::string &msg) { g_err = msg; }
 const std::string &get_last_error() { return g_err; }
@@ -275,38 +289,29 @@ void free_plan(mdpe_plan *p) {
     if (!p) return;
     if (p->device >= 0) {
         DeviceGuard g(p->device);
-        (void)hipFree(p->d_conv);
-        (void)hipFree(p->d_add);
-        (void)hipFree(p->d_stage);
-        (void)hipFree(p->d_out);
-        (void)hipFree(p->d_chains);
-        (void)hipFree(p->d_corr);
-        (void)hipFree(p->d_cbar);
-        (void)hipFree(p->d_zbar);
-        (void)hipFree(p->d_ybar);
-        (void)hipFree(p->d_scale);
-        (void)hipFree(p->d_fconv);
-        (void)hipFree(p->d_foff);
-        (void)hipFree(p->d_fchains);
-        (void)hipFree(p->d_pjobs);
-        (void)hipFree(p->d_pcomps);
-        (void)hipFree(p->d_pcodes);
-        (void)hipFree(p->d_coff);
-        (void)hipFree(p->d_aoff);
-        (void)hipFree(p->d_leaves);
-        (void)hipFree(p->d_chunks);
-        (void)hipFree(p->d_schains);
+        (void)hipFree(p->d_arena);
     }
     delete p;
 }
 
-template <class T>
-int upload(T **dst, const void *src, size_t bytes) {
-    // an empty array still gets a (never read) one-element allocation
-    HIP_TRY(hipMalloc((void **)dst, bytes ? bytes : sizeof(T)));
-    if (src && bytes) HIP_TRY(hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice));
-    return MDPE_OK;
-}
+// The plan's arrays, put together on the host and uploaded as one allocation.
+struct Arena {
+    std::vector<char> bytes;
+    std::vector<std::pair<void **, size_t>> at;  // pointer to set, its offset
+    template <class T>
+    void add(T **dst, const void *src, size_t n) {
+        // an empty array still gets a (never read) element
+        at.push_back({(void **)dst, bytes.size()});
+        bytes.resize(bytes.size() + (std::max(n, sizeof(T)) + 255) / 256 * 256);
+        if (n) std::memcpy(bytes.data() + at.back().second, src, n);
+    }
+    int upload(void **base) {
+        HIP_TRY(hipMalloc(base, bytes.size()));
+        HIP_TRY(hipMemcpy(*base, bytes.data(), bytes.size(), hipMemcpyHostToDevice));
+        for (auto &p : at) *p.first = (char *)*base + p.second;
+        return MDPE_OK;
+    }
+};
 
 int record(mdpe_profiler *prof, int cls, hipStream_t st, bool start) {
     if (!prof || !((prof->classes >> cls) & 1u)) return MDPE_OK;
@@ -332,17 +337,7 @@ int record(mdpe_profiler *prof, int cls, hipStream_t st, bool start) {
         if (e_ != hipSuccess) return fail(MDPE_EDEVICE, std::string(what ": ") + hipGetErrorString(e_)); \
     } while (0)
 
-int simd_count(int device) {
-    static std::atomic<int> cached[kMaxDevices];
-    if (device < 0 || device >= kMaxDevices) return 1024;
-    if (!cached[device]) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
-            cus = 256;
-        cached[device] = 4 * cus;
-    }
-    return cached[device];
-}
+using mdpe::simd_count;
 
 template <int M, bool CORR, bool CX>
 int launch_layer(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipStream_t st, mdpe_profiler *prof) {
@@ -485,15 +480,33 @@ int launch_chain(const mdpe_plan *pl, double *A, hipStream_t st, mdpe_profiler *
 template <int M, bool CX>
 int launch_conv(const mdpe_plan *pl, double *A, hipStream_t st, mdpe_profiler *prof) {
     const mdpe::Plan &P = pl->P;
+    if (P.fused_block_waves > 0) {
+        int rc;
+        if ((rc = record(prof, 1, st, true)) || (rc = mdpe::launch_block_fused(pl, A, st))) return rc;
+        return record(prof, 1, st, false);
+    }
     if (P.fused_components > 0) return launch_fused<M, CX>(pl, A, st, prof);
-    if (P.pipe_layers > 0) {
+    if (P.pipe_r > 0) {
+        int rc;
+        if ((rc = record(prof, 1, st, true)) || (rc = mdpe::launch_block_chain(pl, A, st)) ||
+            (rc = record(prof, 1, st, false)))
+            return rc;
+    } else if (P.pipe_layers > 0) {
         int rc = launch_chain<M, CX>(pl, A, st, prof);
         if (rc) return rc;
     }
     for (int L = P.pipe_layers + 1; L <= P.n_layers(); ++L) {
         const long off = P.conv_off[L - 1];
-        int rc = launch_layer<M, false, CX>(pl, A, pl->d_conv + off, (int)(P.conv_off[L] - off), st, prof);
-        if (rc) return rc;
+        const int nj = (int)(P.conv_off[L] - off);
+        int rc;
+        if (P.block_r > 0) {
+            if (nj == 0) continue;
+            if ((rc = record(prof, 1, st, true)) || (rc = mdpe::launch_block_layer(pl, false, A, pl->d_conv + off, nj, st)) ||
+                (rc = record(prof, 1, st, false)))
+                return rc;
+            continue;
+        }
+        if ((rc = launch_layer<M, false, CX>(pl, A, pl->d_conv + off, nj, st, prof))) return rc;
     }
     return MDPE_OK;
 }
@@ -670,7 +683,12 @@ int adjoint_impl(const mdpe_plan *pl, const double *ybar, void *workspace, const
     }
     if ((rc = record(prof, 0, st, false))) return rc;
     const int nj = (int)P.corr.size();
-    switch (P.m) {
+    if (P.block_r > 0) {
+        if (nj > 0 && ((rc = record(prof, 1, st, true)) || (rc = mdpe::launch_block_layer(pl, true, A, pl->d_corr, nj, st)) ||
+                       (rc = record(prof, 1, st, false))))
+            return rc;
+        rc = MDPE_OK;
+    } else switch (P.m) {
         case 1: rc = launch_layer<1, true, false>(pl, A, pl->d_corr, nj, st, prof); break;
         case 2: rc = launch_layer<2, true, false>(pl, A, pl->d_corr, nj, st, prof); break;
         case 3: rc = launch_layer<3, true, false>(pl, A, pl->d_corr, nj, st, prof); break;
@@ -788,27 +806,31 @@ int plan_polynomial(const mdpe_poly_desc *desc, int device, mdpe_plan **out) {
         pl->add_pass = passes.off;
         int rc;
         mdpe_plan *raw = pl.get();
-        if ((rc = upload(&raw->d_conv, conv.data(), conv.size() * sizeof(int4))) ||
-            (rc = upload(&raw->d_add, add.data(), add.size() * sizeof(int2))) ||
-            (rc = upload(&raw->d_stage, stage.data(), stage.size() * sizeof(int2))) ||
-            (rc = upload(&raw->d_out, P.out_slots.data(), P.out_slots.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_chains, P.lanes.chains.data(), P.lanes.chains.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_corr, corr.data(), corr.size() * sizeof(int4))) ||
-            (rc = upload(&raw->d_cbar, P.coeff_bar_slots.data(), P.coeff_bar_slots.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_zbar, P.z_bar_slots.data(), P.z_bar_slots.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_ybar, &P.ybar_slot, sizeof(int))) ||
-            (rc = upload(&raw->d_scale, scale.data(), scale.size() * sizeof(int4))) ||
-            (rc = upload(&raw->d_fconv, fconv.data(), fconv.size() * sizeof(int4))) ||
-            (rc = upload(&raw->d_foff, P.fused_off.data(), P.fused_off.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_fchains, P.fused_lanes.chains.data(), P.fused_lanes.chains.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_pjobs, pjobs.data(), pjobs.size() * sizeof(int4))) ||
-            (rc = upload(&raw->d_pcomps, P.pipe_comps.data(), P.pipe_comps.size() * sizeof(mdpe::ChainComp))) ||
-            (rc = upload(&raw->d_pcodes, P.pipe_codes.data(), P.pipe_codes.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_leaves, passes.leaves.data(), passes.leaves.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_chunks, passes.chunks.data(), passes.chunks.size() * sizeof(mdpe::AddChunk))) ||
-            (rc = upload(&raw->d_coff, coff.data(), coff.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_aoff, aoff.data(), aoff.size() * sizeof(int))) ||
-            (rc = upload(&raw->d_schains, P.single_lanes.chains.data(), P.single_lanes.chains.size() * sizeof(int)))) {
+        Arena arena;
+        arena.add(&raw->d_conv, conv.data(), conv.size() * sizeof(int4));
+        arena.add(&raw->d_add, add.data(), add.size() * sizeof(int2));
+        arena.add(&raw->d_stage, stage.data(), stage.size() * sizeof(int2));
+        arena.add(&raw->d_out, P.out_slots.data(), P.out_slots.size() * sizeof(int));
+        arena.add(&raw->d_chains, P.lanes.chains.data(), P.lanes.chains.size() * sizeof(int));
+        arena.add(&raw->d_corr, corr.data(), corr.size() * sizeof(int4));
+        arena.add(&raw->d_cbar, P.coeff_bar_slots.data(), P.coeff_bar_slots.size() * sizeof(int));
+        arena.add(&raw->d_zbar, P.z_bar_slots.data(), P.z_bar_slots.size() * sizeof(int));
+        arena.add(&raw->d_ybar, &P.ybar_slot, sizeof(int));
+        arena.add(&raw->d_scale, scale.data(), scale.size() * sizeof(int4));
+        arena.add(&raw->d_fconv, fconv.data(), fconv.size() * sizeof(int4));
+        arena.add(&raw->d_foff, P.fused_off.data(), P.fused_off.size() * sizeof(int));
+        arena.add(&raw->d_fchains, P.fused_lanes.chains.data(), P.fused_lanes.chains.size() * sizeof(int));
+        arena.add(&raw->d_pjobs, pjobs.data(), pjobs.size() * sizeof(int4));
+        arena.add(&raw->d_pcomps, P.pipe_comps.data(), P.pipe_comps.size() * sizeof(mdpe::ChainComp));
+        arena.add(&raw->d_pcodes, P.pipe_codes.data(), P.pipe_codes.size() * sizeof(int));
+        arena.add(&raw->d_blocks, P.blocks.chains.data(), P.blocks.chains.size() * sizeof(int));
+        arena.add(&raw->d_fblocks, P.fused_blocks.chains.data(), P.fused_blocks.chains.size() * sizeof(int));
+        arena.add(&raw->d_leaves, passes.leaves.data(), passes.leaves.size() * sizeof(int));
+        arena.add(&raw->d_chunks, passes.chunks.data(), passes.chunks.size() * sizeof(mdpe::AddChunk));
+        arena.add(&raw->d_coff, coff.data(), coff.size() * sizeof(int));
+        arena.add(&raw->d_aoff, aoff.data(), aoff.size() * sizeof(int));
+        arena.add(&raw->d_schains, P.single_lanes.chains.data(), P.single_lanes.chains.size() * sizeof(int));
+        if ((rc = arena.upload(&raw->d_arena))) {
             std::string keep = g_err;
             free_plan(pl.release());
             g_err = keep;

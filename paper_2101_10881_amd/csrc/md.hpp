@@ -38,21 +38,86 @@ __device__ __forceinline__ void sfor(F &&f) {
     }
 }
 
-__device__ __forceinline__ void two_sum(double a, double b, double &s, double &e) {
-    double ss = a + b;
-    double bb = ss - a;
+// R doubles of R independent coefficients, worked on element by element.  A
+// multiple-double operation on Vec<R> issues every step for all R before the
+// next one, so a dependent FP64 instruction follows R - 1 independent ones: a
+// lone wavefront then no longer waits out each result's latency (a dependent
+// FP64 addition can issue about two issue slots after its operand).
+template <int R>
+struct Vec {
+    double v[R];
+};
+
+#define MDPE_VEC_OP(op)                                                                   \
+    template <int R>                                                                      \
+    __device__ __forceinline__ Vec<R> operator op(const Vec<R> &a, const Vec<R> &b) {     \
+        Vec<R> c;                                                                         \
+        _Pragma("unroll") for (int r = 0; r < R; ++r) c.v[r] = a.v[r] op b.v[r];          \
+        return c;                                                                         \
+    }
+MDPE_VEC_OP(+)
+MDPE_VEC_OP(-)
+MDPE_VEC_OP(*)
+#undef MDPE_VEC_OP
+
+template <int R>
+__device__ __forceinline__ Vec<R> operator*(double a, const Vec<R> &b) {
+    Vec<R> c;
+#pragma unroll
+    for (int r = 0; r < R; ++r) c.v[r] = a * b.v[r];
+    return c;
+}
+template <int R>
+__device__ __forceinline__ Vec<R> operator*(const Vec<R> &a, double b) {
+    Vec<R> c;
+#pragma unroll
+    for (int r = 0; r < R; ++r) c.v[r] = a.v[r] * b;
+    return c;
+}
+template <int R>
+__device__ __forceinline__ Vec<R> operator-(const Vec<R> &a) {
+    Vec<R> c;
+#pragma unroll
+    for (int r = 0; r < R; ++r) c.v[r] = -a.v[r];
+    return c;
+}
+
+__device__ __forceinline__ double md_fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <int R>
+__device__ __forceinline__ Vec<R> md_fma(double a, const Vec<R> &b, const Vec<R> &c) {
+    Vec<R> z;
+#pragma unroll
+    for (int r = 0; r < R; ++r) z.v[r] = __builtin_fma(a, b.v[r], c.v[r]);
+    return z;
+}
+template <int R>
+__device__ __forceinline__ Vec<R> md_fma(const Vec<R> &a, double b, const Vec<R> &c) {
+    Vec<R> z;
+#pragma unroll
+    for (int r = 0; r < R; ++r) z.v[r] = __builtin_fma(a.v[r], b, c.v[r]);
+    return z;
+}
+
+// Every operation below is written once for T = double and T = Vec<R>; the
+// factors X and Y of a product may be one double (shared by the R
+// coefficients) or a Vec.
+template <class T>
+__device__ __forceinline__ void two_sum(T a, T b, T &s, T &e) {
+    T ss = a + b;
+    T bb = ss - a;
     e = (a - (ss - bb)) + (b - bb);
     s = ss;
 }
 
-__device__ __forceinline__ void two_prod(double a, double b, double &p, double &e) {
-    double pp = a * b;
-    e = __builtin_fma(a, b, -pp);
+template <class X, class Y, class T>
+__device__ __forceinline__ void two_prod(X a, Y b, T &p, T &e) {
+    T pp = a * b;
+    e = md_fma(a, b, -pp);
     p = pp;
 }
 
-template <int M, int LO>
-__device__ __forceinline__ void deposit(double (&S)[M], double t) {
+template <int M, int LO, class T>
+__device__ __forceinline__ void deposit(T (&S)[M], T t) {
     if constexpr (LO < M - 1) {
         two_sum(S[LO], t, S[LO], t);
         deposit<M, LO + 1>(S, t);
@@ -61,20 +126,20 @@ __device__ __forceinline__ void deposit(double (&S)[M], double t) {
     }
 }
 
-template <int M>
-__device__ __forceinline__ void renorm(const double (&S)[M], double (&r)[M]) {
+template <int M, class T>
+__device__ __forceinline__ void renorm(const T (&S)[M], T (&r)[M]) {
     if constexpr (M == 1) {
         r[0] = S[0];
     } else {
-        double u[M];
-        double s = S[M - 1];
+        T u[M];
+        T s = S[M - 1];
         sfor<0, M - 1>([&](auto q) {
             constexpr int j = M - 2 - decltype(q)::value;
             two_sum(S[j], s, s, u[j + 1]);
         });
         u[0] = s;
         r[0] = u[0];
-        double e = u[1];
+        T e = u[1];
         sfor<1, M - 1>([&](auto q) {
             constexpr int j = decltype(q)::value;
             two_sum(e, u[j + 1], r[j], e);
@@ -83,9 +148,9 @@ __device__ __forceinline__ void renorm(const double (&S)[M], double (&r)[M]) {
     }
 }
 
-template <int M>
-__device__ __forceinline__ void md_add(const double (&x)[M], const double (&y)[M], double (&z)[M]) {
-    double S[M];
+template <int M, class T>
+__device__ __forceinline__ void md_add(const T (&x)[M], const T (&y)[M], T (&z)[M]) {
+    T S[M];
     sfor<0, M>([&](auto k) { S[decltype(k)::value] = x[decltype(k)::value]; });
     sfor<0, M>([&](auto k) {
         constexpr int K = decltype(k)::value;
@@ -94,10 +159,10 @@ __device__ __forceinline__ void md_add(const double (&x)[M], const double (&y)[M
     renorm<M>(S, z);
 }
 
-template <int M>
-__device__ __forceinline__ void md_mul(const double (&x)[M], const double (&y)[M], double (&z)[M]) {
-    double S[M];
-    double E[M > 1 ? M - 1 : 1];
+template <int M, class X, class Y, class T>
+__device__ __forceinline__ void md_mul(const X (&x)[M], const Y (&y)[M], T (&z)[M]) {
+    T S[M];
+    T E[M > 1 ? M - 1 : 1];
     sfor<0, M - 1>([&](auto k) {
         constexpr int K = decltype(k)::value;
         two_prod(x[0], y[K], S[K], E[K]);
@@ -105,11 +170,11 @@ __device__ __forceinline__ void md_mul(const double (&x)[M], const double (&y)[M
     S[M - 1] = x[0] * y[M - 1];
     sfor<1, M>([&](auto i) {
         constexpr int I = decltype(i)::value;
-        S[M - 1] = __builtin_fma(x[I], y[M - 1 - I], S[M - 1]);
+        S[M - 1] = md_fma(x[I], y[M - 1 - I], S[M - 1]);
     });
     sfor<1, M>([&](auto i) {
         constexpr int I = decltype(i)::value;
-        S[M - 1] = __builtin_fma(x[I], y[M - I], S[M - 1]);
+        S[M - 1] = md_fma(x[I], y[M - I], S[M - 1]);
     });
     sfor<0, M - 1>([&](auto k) {
         constexpr int K = decltype(k)::value;
@@ -119,7 +184,7 @@ __device__ __forceinline__ void md_mul(const double (&x)[M], const double (&y)[M
         constexpr int K = decltype(k)::value;
         sfor<1, K + 1>([&](auto i) {
             constexpr int I = decltype(i)::value;
-            double p, e;
+            T p, e;
             two_prod(x[I], y[K - I], p, e);
             deposit<M, K>(S, p);
             deposit<M, K + 1>(S, e);
@@ -132,9 +197,10 @@ __device__ __forceinline__ void md_mul(const double (&x)[M], const double (&y)[M
 template <int M, bool CX>
 constexpr int kCoef = CX ? 2 * M : M;
 
-template <int M>
-__device__ __forceinline__ void cmd_mul(const double (&x)[2 * M], const double (&y)[2 * M], double (&z)[2 * M]) {
-    double xr[M], xi[M], yr[M], yi[M];
+template <int M, class X, class Y, class T>
+__device__ __forceinline__ void cmd_mul(const X (&x)[2 * M], const Y (&y)[2 * M], T (&z)[2 * M]) {
+    X xr[M], xi[M];
+    Y yr[M], yi[M];
     sfor<0, M>([&](auto l) {
         constexpr int L = decltype(l)::value;
         xr[L] = x[L];
@@ -142,7 +208,7 @@ __device__ __forceinline__ void cmd_mul(const double (&x)[2 * M], const double (
         yr[L] = y[L];
         yi[L] = y[M + L];
     });
-    double rr[M], ii[M], ri[M], ir[M], zr[M], zi[M];
+    T rr[M], ii[M], ri[M], ir[M], zr[M], zi[M];
     md_mul<M>(xr, yr, rr);
     md_mul<M>(xi, yi, ii);
     md_mul<M>(xr, yi, ri);
@@ -157,9 +223,9 @@ __device__ __forceinline__ void cmd_mul(const double (&x)[2 * M], const double (
     });
 }
 
-template <int M>
-__device__ __forceinline__ void cmd_add(const double (&x)[2 * M], const double (&y)[2 * M], double (&z)[2 * M]) {
-    double xr[M], xi[M], yr[M], yi[M], zr[M], zi[M];
+template <int M, class T>
+__device__ __forceinline__ void cmd_add(const T (&x)[2 * M], const T (&y)[2 * M], T (&z)[2 * M]) {
+    T xr[M], xi[M], yr[M], yi[M], zr[M], zi[M];
     sfor<0, M>([&](auto l) {
         constexpr int L = decltype(l)::value;
         xr[L] = x[L];
@@ -177,18 +243,18 @@ __device__ __forceinline__ void cmd_add(const double (&x)[2 * M], const double (
 }
 
 // One coefficient operation of the series' number field.
-template <int M, bool CX>
-__device__ __forceinline__ void coef_mul(const double (&x)[kCoef<M, CX>], const double (&y)[kCoef<M, CX>],
-                                         double (&z)[kCoef<M, CX>]) {
+template <int M, bool CX, class X, class Y, class T>
+__device__ __forceinline__ void coef_mul(const X (&x)[kCoef<M, CX>], const Y (&y)[kCoef<M, CX>],
+                                         T (&z)[kCoef<M, CX>]) {
     if constexpr (CX)
         cmd_mul<M>(x, y, z);
     else
         md_mul<M>(x, y, z);
 }
 
-template <int M, bool CX>
-__device__ __forceinline__ void coef_add(const double (&x)[kCoef<M, CX>], const double (&y)[kCoef<M, CX>],
-                                         double (&z)[kCoef<M, CX>]) {
+template <int M, bool CX, class T>
+__device__ __forceinline__ void coef_add(const T (&x)[kCoef<M, CX>], const T (&y)[kCoef<M, CX>],
+                                         T (&z)[kCoef<M, CX>]) {
     if constexpr (CX)
         cmd_add<M>(x, y, z);
     else

@@ -30,6 +30,7 @@
 
 #include <algorithm>
 #include <numeric>
+#include <set>
 #include <unordered_map>
 
 namespace mdpe {
@@ -47,9 +48,11 @@ int choose_jobs_per_group(int d, int w) {
     return (int)std::max(1L, std::min((long)need, cap));
 }
 
-LaneSchedule make_lane_schedule(int d, int J, int Q) {
-    // Assign the J*(d+1) output coefficients (coefficient k costs k+1
-    // multiply-adds) to the 64*Q lanes of Q wavefronts: first-fit-decreasing
+// J jobs of `lengths.size()` items each (item k takes lengths[k] steps,
+// nondecreasing in k) over the lanes of Q wavefronts.
+static LaneSchedule pack_items(const std::vector<int> &lengths, int J, int Q) {
+    // Assign the items (output coefficients: coefficient k costs k+1
+    // multiply-adds; or blocks of them) to the 64*Q lanes of Q wavefronts: first-fit-decreasing
     // into lanes of capacity C, for the smallest C >= max(ceil(total/lanes),
     // d+1) that fits.  Each coefficient stays whole on one lane, so its
     // operation order is the specified one whatever lane computes it.
@@ -60,14 +63,14 @@ LaneSchedule make_lane_schedule(int d, int J, int Q) {
     std::vector<std::pair<int, int>> items;  // (length, code)
     long total = 0;
     for (int j = 0; j < J; ++j)
-        for (int k = 0; k <= d; ++k) {
-            items.push_back({k + 1, (j << 16) | k});
-            total += k + 1;
+        for (size_t k = 0; k < lengths.size(); ++k) {
+            items.push_back({lengths[k], (j << 16) | (int)k});
+            total += lengths[k];
         }
     std::stable_sort(items.begin(), items.end(), [](auto &a, auto &b) { return a.first > b.first; });
     std::vector<long> load;
     std::vector<std::vector<int32_t>> lists;
-    for (long cap = std::max((total + lanes - 1) / lanes, (long)d + 1);; ++cap) {
+    for (long cap = std::max((total + lanes - 1) / lanes, (long)lengths.back());; ++cap) {
         load.assign(lanes, 0);
         lists.assign(lanes, {});
         bool ok = true;
@@ -91,6 +94,18 @@ LaneSchedule make_lane_schedule(int d, int J, int Q) {
     for (int l = 0; l < lanes; ++l)
         for (size_t q = 0; q < lists[l].size(); ++q) s.chains[(size_t)l * stride + q] = lists[l][q];
     return s;
+}
+
+LaneSchedule make_lane_schedule(int d, int J, int Q) {
+    std::vector<int> lengths(d + 1);
+    std::iota(lengths.begin(), lengths.end(), 1);
+    return pack_items(lengths, J, Q);
+}
+
+LaneSchedule make_block_schedule(int d, int R, int U, int J, int Q) {
+    std::vector<int> lengths;
+    for (int k = 0; k <= d; k += R) lengths.push_back(k / U + 1);
+    return pack_items(lengths, J, Q);
 }
 
 LaneSchedule make_paired_schedule(int d, int Q) {
@@ -336,6 +351,133 @@ static void choose_staged_lanes(Plan &P, int from_layer) {
         consider(make_lane_schedule(d, 1, Q), true, layer_cost(P, Q, 1, dealt_steps(d, 1, Q), w == 1 ? 0.15 : 0.4, from_layer));
 }
 
+// FP64 instructions of one multiply-add of the plan's number field.
+static long md_instr(bool mul, int m);
+static long mac_instr(const Plan &P) {
+    const long mul = md_instr(true, P.m), add = md_instr(false, P.m);
+    return P.complex_series() ? 4 * mul + 4 * add : mul + add;
+}
+
+// Cycles of one iteration of the blocked convolution (R coefficients, U terms)
+// with k wavefronts on a SIMD: the FP64 instructions, the selects of first and
+// dropped terms and ~40 instructions of addresses and item switch, 4.4 cycles
+// each, for every wavefront (measured: two or more wavefronts issue one
+// instruction every 4.4 to 5 cycles between them, a lone one every 7, 6 and 5.5
+// cycles at R = 1, 2 and 4), and a lone one also waits for its operands.
+static double block_iteration(const Plan &P, int R, int U, double k) {
+    const int w = P.w;
+    const double instr = (double)R * U * mac_instr(P) + 2.0 * w * R + (R == 1 ? 2.0 * w * (U - 1) : 1.0 * w * R * (R - 1)) +
+                         1.0 * U * w + 40;
+    const double lone = R == 1 ? 1.5 : R == 2 ? 1.4 : 1.25, share = R > 1 ? 1.0 : k < 3 ? 1.08 : 1.04;
+    return std::max(4.4 * instr * share * k, 4.4 * instr * lone + 350);
+}
+
+static double block_cost(const Plan &P, int R, int U, const LaneSchedule &ls, int from_layer) {
+    double c = 0;
+    for (int L = from_layer; L <= P.n_layers(); ++L) {
+        const long jobs = P.conv_off[L] - P.conv_off[L - 1];
+        const long waves = (jobs + ls.jobs_per_group - 1) / ls.jobs_per_group * ls.waves_per_job;
+        c += ls.steps * block_iteration(P, R, U, (double)((waves + kSimds - 1) / kSimds));
+    }
+    return c;
+}
+
+// The blocked kernels address the workspace by 32-bit byte offsets.
+bool small_workspace(const Plan &P) {
+    return P.n_series * (int64_t)(P.d + 1) * P.w * 8 <= 0xffff0000LL;
+}
+
+// Whether reading `over` coefficients before and past the second operand of
+// every job stays inside the workspace.
+bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs, int over) {
+    for (const auto &t : jobs)
+        if ((int64_t)t[1] * (P.d + 1) < over || (P.n_series - 1 - t[1]) * (int64_t)(P.d + 1) < over) return false;
+    return true;
+}
+
+// Whether the staged launches of width w and degree d run blocks.  Against the
+// coefficient-by-coefficient kernel (p1, d = 8 / 31 / 63 / 95 / 152, wall time):
+// two doubles per coefficient 1.27 / 0.99 / 1.33 / 1.18 / 1.31 times as fast,
+// (one: 0.86 to 0.93 at d = 31 to 95 on p1's layers of up to 5460 jobs, 1.06 to
+// 1.16 on p3's of 16256, 1.1 from d = 128 on),
+// three 1.51 / 1.10 / 1.18 / 1.13 / 1.10, four 1.39 / 1.04 / 1.09 / 1.06 / 1.05,
+// five 1.30 / 1.02 / 1.04 / 1.02 / 0.98, eight 1.09 / 1.00 / 0.99 / 0.98 / 0.99:
+// what blocks save is the ~60 instructions a step spends around its
+// arithmetic, 1124 instructions at eight doubles, where the other kernel's
+// overlap of a product with the sum before it is worth more.
+static bool blocks_pay(const Plan &P) {
+    if (P.streamed || !small_workspace(P)) return false;
+    if (P.w > 1) return P.w <= 4 || (P.w == 5 && P.d <= 127) || P.d <= 16;
+    long most = 0;
+    for (int L = 1; L <= P.n_layers(); ++L) most = std::max(most, (long)(P.conv_off[L] - P.conv_off[L - 1]));
+    return P.d >= 128 || most > 6144;
+}
+
+// Blocks of R coefficients per lane, U terms an iteration, for the staged
+// per-layer launches (conv_block.hpp) of the layers from_layer..., J jobs per
+// wavefront and Q wavefronts per job, by the estimated cycles of the layers.
+// One coefficient and four terms at up to two doubles per coefficient, two
+// terms beyond (four coefficients and terms too at one double, where loads
+// count: p1 d = 152 1.13 against 0.94 times the other kernel's speed; tiles of
+// 2 x 2 measured slower nearly everywhere: they halve the wavefronts).
+static void choose_block_lanes(Plan &P, int from_layer) {
+    P.block_r = P.block_u = 0;
+    P.blocks = LaneSchedule();
+    if (!blocks_pay(P)) return;
+    const int w = P.w;
+    const int maxq = P.lanes.waves_per_job > 1 ? 4 : 1;
+    double best = -1;
+    for (int R : {1, 4}) {
+        const int U = w <= 2 ? 4 : 2;
+        if (R == 4 && w > 1) continue;
+        // second operands in global memory are read up to U - 1 coefficients
+        // past either end
+        if (!stages_second_operand(w) && !(reads_inside(P, P.conv, U - 1) && reads_inside(P, P.corr, U - 1))) continue;
+        const long longest = P.d / U + 1, items = P.d / R + 1;
+        for (int J : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64}) {
+            if (block_group_bytes(P.d + 1, w, U, J) > kLdsBudget && J > 1) break;
+            if (block_group_bytes(P.d + 1, w, U, J) > kMaxLdsBytes) break;
+            if ((long)(J - 1) * items * (longest + 1) / 2 > (long)kLanes * (longest + 1)) break;
+            for (int Q = 1; Q <= (J == 1 ? maxq : 1); ++Q) {
+                LaneSchedule ls = make_block_schedule(P.d, R, U, J, Q);
+                const double c = block_cost(P, R, U, ls, from_layer);
+                if (best < 0 || c < best) {
+                    best = c;
+                    P.blocks = std::move(ls);
+                    P.block_r = R;
+                    P.block_u = U;
+                }
+            }
+        }
+    }
+}
+
+// The fused launch by blocks: J of a component's at most `widest` jobs per
+// wavefront and as many wavefronts as that takes.
+static void choose_fused_blocks(Plan &P, int widest) {
+    P.fused_block_waves = 0;
+    // p1, against one job per wavefront by coefficients: two doubles 1.07 times as
+    // fast at d = 8, 1.21 at d = 31, 0.95 at d = 63; one double 0.57 to 0.9; 210
+    // products of four of ten variables at three to five doubles 1.10 to 1.18
+    if (P.w == 1 || P.w > 5 || (P.w == 2 && P.d > 40) || !blocks_pay(P) || widest < 1) return;
+    const int U = P.w <= 2 ? 4 : 2;
+    if (!stages_second_operand(P.w) && !reads_inside(P, P.conv, U - 1)) return;
+    double best = -1;
+    for (int waves = 1; waves <= 4; ++waves) {
+        const int J = std::min((widest + waves - 1) / waves, 16);
+        if (waves * ((block_group_bytes(P.d + 1, P.w, U, J) + 15) / 16 * 16) > kMaxLdsBytes) continue;
+        LaneSchedule ls = make_block_schedule(P.d, 1, U, J, 1);
+        const int rounds = (widest + waves * J - 1) / (waves * J);
+        const double k = std::min(8.0, std::max(1.0, (double)P.fused_components * waves / kSimds));
+        const double c = rounds * ls.steps * block_iteration(P, 1, U, k) * std::max(1.0, (double)P.fused_components * waves / kSimds / 8.0);
+        if (best < 0 || c < best) {
+            best = c;
+            P.fused_blocks = std::move(ls);
+            P.fused_block_waves = waves;
+        }
+    }
+}
+
 // Layer balancing.  The layering above puts every convolution at its
 // earliest layer; many jobs have slack (b_1 of a four-variable monomial is
 // needed only by b_2, c_1 by nothing but the additions), and any layering
@@ -454,17 +596,13 @@ static bool balance_layers(Plan &P, long per_round) {
     return true;
 }
 
-// Fused layers: split the convolutions into independent components.  Two jobs
-// depend on each other only through a slot that some convolution writes (the
-// staged inputs a_k and z_i are read-only), so a union of every job's output
-// slot with each operand slot that is also written puts every read after
-// write, write after write and write after read pair in one component.  The
-// layers inside a component keep the plan's order.
-// Returns the most jobs of one component in one layer (0 if nothing was fused).
-static int fuse_layers(Plan &P) {
-    const int nl = P.n_layers();
+// Independent components of the convolutions.  Two jobs depend on each other
+// only through a slot that some convolution writes (the staged inputs a_k and
+// z_i are read-only), so a union of every job's output slot with each operand
+// slot that is also written puts every read after write, write after write and
+// write after read pair in one component.  Numbered by their first job.
+int32_t job_components(const Plan &P, std::vector<int32_t> &comp) {
     const size_t nj = P.conv.size();
-    if (nl < 1 || nj == 0) return 0;
     std::vector<int64_t> parent(P.n_series);
     for (int64_t s = 0; s < P.n_series; ++s) parent[s] = s;
     auto find = [&](int64_t s) {
@@ -479,13 +617,26 @@ static int fuse_layers(Plan &P) {
                 const int64_t a = find(t[o]), b = find(t[2]);
                 if (a != b) parent[a] = b;
             }
-    std::vector<int32_t> comp_of_root(P.n_series, -1), comp(nj);
+    std::vector<int32_t> comp_of_root(P.n_series, -1);
+    comp.resize(nj);
     int32_t C = 0;
     for (size_t j = 0; j < nj; ++j) {
         const int64_t r = find(P.conv[j][2]);
         if (comp_of_root[r] < 0) comp_of_root[r] = C++;
         comp[j] = comp_of_root[r];
     }
+    return C;
+}
+
+// Fused layers: the jobs by independent component; the layers inside a
+// component keep the plan's order.
+// Returns the most jobs of one component in one layer (0 if nothing was fused).
+static int fuse_layers(Plan &P) {
+    const int nl = P.n_layers();
+    const size_t nj = P.conv.size();
+    if (nl < 1 || nj == 0) return 0;
+    std::vector<int32_t> comp;
+    const int32_t C = job_components(P, comp);
     std::vector<int> layer(nj);
     for (int L = 1; L <= nl; ++L)
         for (int64_t j = P.conv_off[L - 1]; j < P.conv_off[L]; ++j) layer[j] = L;
@@ -515,6 +666,7 @@ static int fuse_layers(Plan &P) {
     // up to four wavefronts (one per SIMD of a CU); the launcher lowers this
     // where their LDS would not fit
     P.fused_waves = std::min(4, std::max(1, widest));
+    choose_fused_blocks(P, widest);
     return widest;
 }
 
@@ -524,6 +676,8 @@ static void unfuse(Plan &P) {
     P.fused_components = P.fused_waves = 0;
     P.fused_lanes = LaneSchedule();
     P.fused_simple = false;
+    P.fused_block_waves = 0;
+    P.fused_blocks = LaneSchedule();
 }
 
 // Fuse the layers by default where each layer is a short step that the per-layer
@@ -562,7 +716,7 @@ static bool fuse_by_default(const Plan &P) {
 
 static inline int chain_window(int it, int S) { return it >= 0 ? it / S : -1; }
 
-int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> &codes, int *stride) {
+int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> &codes, int *stride, int U) {
     // Jobs in chain order, each job's coefficients longest first; each at the
     // earliest step its first operand allows (every x_i read after the window
     // of its store by the previous job; its own store into the LDS slot of
@@ -570,40 +724,46 @@ int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> 
     // earlier), on the lane free by then with the least idle time before it,
     // else on the lane that frees first.
     const int lanes = kLanes * W, d1 = d + 1;
-    std::vector<int> lane_free(lanes, 0);
+    std::set<std::pair<int, int>> lane_free;  // (free from, -lane)
+    for (int q = 0; q < lanes; ++q) lane_free.insert({0, -q});
     std::vector<std::vector<int32_t>> lists(lanes);
-    std::vector<int> store((size_t)L * d1, 0);
+    std::vector<int> store((size_t)L * d1, 0), ready(d1);
     std::vector<int> last_read(L, -1);
     for (int l = 0; l < L; ++l) {
-        for (int k = d; k >= 0; --k) {
-            int s0 = 0;
+        // ready[k]: the earliest start of coefficient k by its first operand
+        for (int k = 0; k <= d; ++k) {
+            ready[k] = k > 0 ? ready[k - 1] : 0;
             if (l > 0)
-                for (int i = 0; i <= k; ++i)
-                    s0 = std::max(s0, S * (chain_window(store[(size_t)(l - 1) * d1 + i], S) + 1) - i + 1);
-            if (l + 1 < L && l + 1 - B >= 0) s0 = std::max(s0, S * (chain_window(last_read[l + 1 - B], S) + 1) - k);
-            int best = -1;
-            for (int q = 0; q < lanes; ++q)
-                if (lane_free[q] <= s0 && (best < 0 || lane_free[q] > lane_free[best])) best = q;
-            if (best < 0) {
-                best = 0;
-                for (int q = 1; q < lanes; ++q)
-                    if (lane_free[q] < lane_free[best]) best = q;
+                ready[k] = std::max(ready[k], S * (chain_window(store[(size_t)(l - 1) * d1 + k], S) + 1) - k / U + 1);
+        }
+        for (int k = d; k >= 0; --k) {
+            int s0 = ready[k];
+            if (l + 1 < L && l + 1 - B >= 0) s0 = std::max(s0, S * (chain_window(last_read[l + 1 - B], S) + 1) - k / U);
+            auto it = lane_free.upper_bound({s0, 1});
+            if (it != lane_free.begin()) {
+                --it;  // the latest free time up to s0, its first lane
+            } else {
+                it = lane_free.begin();
+                const int t = it->first;  // the earliest free time, its first lane
+                it = std::prev(lane_free.upper_bound({t, 1}));
             }
-            const int start = std::max(s0, lane_free[best]);
-            for (int g = start - lane_free[best]; g > 0;) {
+            const int from = it->first, best = -it->second;
+            lane_free.erase(it);
+            const int start = std::max(s0, from);
+            for (int g = start - from; g > 0;) {
                 const int q = std::min(g, 0x10000);
                 lists[best].push_back((kIdleJob << 16) | (q - 1));
                 g -= q;
             }
             lists[best].push_back((l << 16) | k);
-            lane_free[best] = start + k + 1;
-            store[(size_t)l * d1 + k] = start + k;
-            last_read[l] = std::max(last_read[l], start + k - 1);
+            lane_free.insert({start + k / U + 1, -best});
+            store[(size_t)l * d1 + k] = start + k / U;
+            last_read[l] = std::max(last_read[l], start + k / U - 1);
         }
     }
     // a multiple of the window, and even (the kernel may run two steps per iteration)
     const int q = S % 2 ? 2 * S : S;
-    int steps = *std::max_element(lane_free.begin(), lane_free.end());
+    int steps = lane_free.rbegin()->first;
     steps = (steps + q - 1) / q * q;
     size_t st = 1;
     for (auto &x : lists) st = std::max(st, x.size() + 1);
@@ -613,7 +773,8 @@ int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> 
     return steps;
 }
 
-std::string check_chain_schedule(int L, int d, int W, int S, int B, int steps, const int32_t *codes, int stride) {
+std::string check_chain_schedule(int L, int d, int W, int S, int B, int steps, const int32_t *codes, int stride,
+                                 int U) {
     if (L < 1 || L > kMaxChainLength || d < 0 || W < 1 || W > 16 || S < 1 || B < 2 || steps < 0 || steps % S ||
         stride < 1 || !codes)
         return "bad chain schedule parameters";
@@ -633,7 +794,7 @@ std::string check_chain_schedule(int L, int d, int W, int S, int B, int steps, c
             const size_t key = (size_t)j * d1 + k;
             if (start[key] >= 0) return "coefficient scheduled twice";
             start[key] = (int)t;
-            t += k + 1;
+            t += k / U + 1;
         }
         if (e == stride) return "row without its terminator";
         if (t > steps) return "row longer than the steps";
@@ -644,14 +805,14 @@ std::string check_chain_schedule(int L, int d, int W, int S, int B, int steps, c
         for (int k = 0; k <= d; ++k) {
             const int s = start[(size_t)l * d1 + k];
             for (int i = 0; i <= k; ++i) {
-                const int rd = s + i - 1;  // iteration that reads x_i
+                const int rd = s + i / U - 1;  // iteration that reads x_i
                 // job 0's first operand is staged before the first barrier
-                if (l > 0 && chain_window(rd, S) <= chain_window(start[(size_t)(l - 1) * d1 + i] + i, S))
+                if (l > 0 && chain_window(rd, S) <= chain_window(start[(size_t)(l - 1) * d1 + i] + i / U, S))
                     return "job " + std::to_string(l) + " coefficient " + std::to_string(k) +
                            ": first operand read before the barrier after its store";
                 // job l-1+B stores the first operand of job l+B into the same slot
                 const int wj = l - 1 + B;
-                if (wj + 1 < L && chain_window(start[(size_t)wj * d1 + i] + i, S) <= chain_window(rd, S))
+                if (wj + 1 < L && chain_window(start[(size_t)wj * d1 + i] + i / U, S) <= chain_window(rd, S))
                     return "job " + std::to_string(l) + " coefficient " + std::to_string(k) +
                            ": first operand overwritten before the barrier after its read";
             }
@@ -690,12 +851,23 @@ static bool find_chains(const Plan &P, std::vector<std::vector<int64_t>> &chains
     return !chains.empty();
 }
 
+// Estimated cycles of the per-layer launches of the layers from_layer...: their
+// arithmetic and ~4.5 us (10000 cycles) of launch boundary each.
+static double layers_cost(const Plan &P, int from_layer) {
+    const double launches = 10000.0 * (P.n_layers() - from_layer + 1);
+    if (P.block_r > 0) return launches + block_cost(P, P.block_r, P.block_u, P.blocks, from_layer);
+    const int Q = P.lanes.waves_per_job, J = P.lanes.jobs_per_group;
+    if (P.simple)
+        return launches + layer_cost(P, Q, J, dealt_steps(P.d, J, Q), 4.4 * (mac_instr(P) + 10), from_layer);
+    return launches + layer_cost(P, Q, J, P.lanes.steps, 4.4 * (mac_instr(P) + 90), from_layer);
+}
+
 // Rebuilds P's convolution layers for the chain launch with W wavefronts per
-// chain, a barrier every S steps and B LDS slots of first operands: layer L
-// <= pipe_layers holds the jobs at position L of their chain, the other jobs
-// follow at their earliest layers.  Returns the estimated cost (in wavefront
-// steps per SIMD, the unit of layer_cost) or -1 when no chain launch applies.
-static double make_chain_plan(Plan &P, const std::vector<std::vector<int64_t>> &chains, int W, int S, int B) {
+// chain, a barrier every S steps and B LDS slots of first operands, by
+// coefficients (R = 0) or blocks of R, U terms an iteration: layer L <= pipe_layers holds the jobs at
+// position L of their chain, the other jobs follow at their earliest layers.
+static bool make_chain_plan(Plan &P, const std::vector<std::vector<int64_t>> &chains, int R, int U, int W, int S,
+                            int B) {
     const size_t nj = P.conv.size();
     int Lmax = 0;
     std::vector<char> in_chain(nj, 0);
@@ -727,26 +899,33 @@ static double make_chain_plan(Plan &P, const std::vector<std::vector<int64_t>> &
             if (!in_chain[j] && rest_layer[j] == L) conv.push_back(P.conv[j]);
         off.push_back((int64_t)conv.size());
     }
-    if (conv.size() != nj) return -1;
+    if (conv.size() != nj) return false;
     // one schedule per chain length
+    const int dd = R > 0 ? P.d / R : P.d;
     std::vector<ChainComp> comps;
     std::vector<std::array<int32_t, 3>> pjobs;
     std::vector<int32_t> codes;
     std::vector<std::array<int, 3>> sched(Lmax + 1, {-1, 0, 0});  // length -> {code_off, stride, steps}
-    int worst = 0;
-    for (auto &c : chains) {
+    // longest chains first: they start first
+    std::vector<size_t> order(chains.size());
+    std::iota(order.begin(), order.end(), (size_t)0);
+    if (R > 0)
+        std::stable_sort(order.begin(), order.end(),
+                         [&](size_t a, size_t b) { return chains[a].size() > chains[b].size(); });
+    for (size_t o : order) {
+        const auto &c = chains[o];
         const int len = (int)c.size();
         if (sched[len][0] < 0) {
             std::vector<int32_t> cs;
             int stride = 0;
-            const int steps = make_chain_schedule(len, P.d, W, S, B, cs, &stride);
-            if (!check_chain_schedule(len, P.d, W, S, B, steps, cs.data(), stride).empty()) return -1;
-            if (codes.size() + cs.size() > (size_t)INT32_MAX / 2) return -1;
+            const int u = R == 1 ? U : 1;  // tiles: an iteration is a step over blocks
+            const int steps = make_chain_schedule(len, dd, W, S, B, cs, &stride, u);
+            if (!check_chain_schedule(len, dd, W, S, B, steps, cs.data(), stride, u).empty()) return false;
+            if (codes.size() + cs.size() > (size_t)INT32_MAX / 2) return false;
             sched[len] = {(int)codes.size(), stride, steps};
             codes.insert(codes.end(), cs.begin(), cs.end());
         }
         comps.push_back(ChainComp{(int32_t)pjobs.size(), len, sched[len][0], sched[len][1], sched[len][2], 0, 0, 0});
-        worst = std::max(worst, sched[len][2]);
         for (int64_t j : c) pjobs.push_back(P.conv[j]);
     }
     P.conv.swap(conv);
@@ -755,56 +934,39 @@ static double make_chain_plan(Plan &P, const std::vector<std::vector<int64_t>> &
     P.pipe_waves = W;
     P.pipe_window = S;
     P.pipe_ring = B;
+    P.pipe_r = R;
+    P.pipe_u = U;
     P.pipe_jobs.swap(pjobs);
     P.pipe_comps.swap(comps);
     P.pipe_codes.swap(codes);
     P.balanced = false;
     choose_staged_lanes(P, Lmax + 1);
-    // a chain's workgroup holds a CU: k = W/4 wavefronts per SIMD, ceil(chains
-    // / CUs) rounds.  A lone wavefront keeps its SIMD's VALU about half busy
-    // (counters on c2: 0.49); k of them share it at eff(k) of k times the
-    // lone step's cost (measured on p2 at d = 31..152 and four, eight and ten
-    // doubles, the same schedules at 4..16 wavefronts: eff(2) = 0.80, eff(3)
-    // = 0.73, eff(4) = 0.70 up to five doubles per coefficient; 0.89, 0.81,
-    // 0.74 from eight on, where one step is long enough to fill the pipeline
-    // better).
+    choose_block_lanes(P, Lmax + 1);
+    return true;
+}
+
+// Estimated cycles of the chain launch: its iterations, and a barrier's wait for
+// the slowest of W wavefronts (measured on p2: quad double, d = 64, 320
+// iterations on 8 wavefronts 348 us; penta double, d = 37, 222 on 4 245 us).
+static double chain_cost(const Plan &P, size_t chains, int R, int U, int W, int S, int steps, long lds) {
+    // workgroups of a CU, by LDS and by 16 wavefronts (128 VGPRs each)
     const long cus = kSimds / 4;
-    const double rounds = std::ceil((double)chains.size() / cus);
-    const int k = std::max(1, W / 4);
-    static const double eff_short[5] = {1.0, 1.0, 0.80, 0.73, 0.70}, eff_long[5] = {1.0, 1.0, 0.89, 0.81, 0.74};
-    const double eff = P.w >= 8 ? eff_long[std::min(k, 4)] : eff_short[std::min(k, 4)];
-    // a chain step at one double per coefficient costs about 0.55 of a
-    // schedule step (measured on p2 at d = 8..152 against the dealt plans)
-    const double step = P.w == 1 ? 0.55 : 1.0;
-    const double chain_cost = rounds * worst * k * eff * (1.0 + 0.02 * 4.0 / S) * step;
-    // the layers after the chains (p2's cross products), dealt or by the lane
-    // schedule as choose_staged_lanes set them, weighed as the plan without a
-    // chain launch weighs its steps
-    const int Q = P.lanes.waves_per_job, J = P.lanes.jobs_per_group;
-    const double rest = P.simple ? layer_cost(P, Q, J, dealt_steps(P.d, J, Q), P.w == 1 ? 0.15 : 0.4, Lmax + 1)
-                                 : layer_cost(P, Q, J, P.lanes.steps, 1.0, Lmax + 1);
-    return chain_cost + rest;
+    const long fit = std::max(1L, std::min((long)kMaxLdsBytes / lds, 16L / W));
+    const long per_cu = std::min(fit, ((long)chains + cus - 1) / cus);
+    const double rounds = std::ceil(chains / (double)(cus * per_cu));
+    const double k = std::max(1.0, per_cu * W / 4.0);  // wavefronts per SIMD
+    return rounds * steps * (block_iteration(P, R, U, k) + (W > 1 ? (60.0 + 30.0 * W) / S : 0));
 }
 
-// LDS slots of first operands a chain workgroup gets: up to 96 KiB of LDS
-// (one workgroup per CU then), at least two, at most the longest chain.
-static int chain_ring_slots(const Plan &P, int Lmax) {
-    const long per = (long)(P.d + 1) * P.w * 8;
-    const long jobs = (long)Lmax * 32;
-    const long fit = (98304 - jobs) / per;
-    return (int)std::min<long>(std::max(Lmax, 2), fit);
-}
-
-// The chain launch for a plan without in-place jobs: the cheapest of W = 4,
-// 8, 12, 16 wavefronts and barriers every S = 1, 2, 4 steps, applied when forced or
-// estimated under 0.9 of `other` (the cost of the plan without it).  On p2
-// (64 products per chain) that is every precision from two doubles on at
-// d = 8..191 (measured 1.3-7.4x faster) and one double at d = 31..152
-// (1.1-1.6x); one double at d = 191 keeps its dealt per-layer plan (the chain
-// launch measured 7% slower there).  Returns whether P now holds a chain
-// launch.
-static constexpr bool kChainByDefault = true;
-
+// The chain launch for a plan without in-place jobs: the cheapest estimate
+// over R coefficients per block, W wavefronts per chain, a barrier every S
+// iterations and the LDS of a chain, applied when forced or estimated under 0.9
+// of `other` (the cycles of the plan without it).  Returns whether P now holds
+// a chain launch.  Chains from nine products on: shorter ones (p1's four, the
+// batched instances' at most eight) have too few layers to save; below 16
+// products from 64 chains on (211 monomials of 1 to 12 variables, five doubles,
+// d = 37: 404 -> 130 us): plans of a few short chains keep their layers and
+// their series count.
 static bool choose_chain_launch(Plan &P, bool forced, double other) {
     if (P.streamed) return false;
     std::vector<std::vector<int64_t>> chains;
@@ -815,26 +977,58 @@ static bool choose_chain_launch(Plan &P, bool forced, double other) {
         Lmax = std::max(Lmax, (int)c.size());
         members += (long)c.size();
     }
-    if (!forced && (Lmax < 16 || 4 * members < (long)P.conv.size())) return false;
-    const int B = chain_ring_slots(P, Lmax);
-    if (B < 2) return false;
+    if (!forced && (Lmax < 9 || (Lmax < 16 && chains.size() < 64) || 4 * members < (long)P.conv.size())) return false;
+    // (one double per coefficient beyond d = 160 keeps the layered plan unless asked)
+    if (!forced && P.w == 1 && P.d > 160) return false;
     double best = -1;
-    int bw = 0, bs = 0;
-    // up to 16 wavefronts (1024 threads, at most 128 VGPRs each: not for ten
-    // doubles per coefficient, whose chain kernel needs 134)
-    for (int W : {4, 8, 12, 16})
-        for (int S : {1, 2, 4}) {
-            if (W == 16 && P.w > 8) continue;
-            Plan T = P;
-            const double c = make_chain_plan(T, chains, W, S, B);
-            if (c >= 0 && (best < 0 || c < best)) {
-                best = c;
-                bw = W;
-                bs = S;
+    int br = 0, bu = 0, bw = 0, bs = 0, bb = 0;
+    // by coefficients (R = 0, the 64-bit addresses) where the workspace is 4 GiB or more
+    const bool small = small_workspace(P);
+    static const int kRU[5][2] = {{0, 0}, {1, 1}, {1, 2}, {2, 2}, {4, 4}};
+    for (auto &ru : kRU) {
+        const int R = ru[0], U = ru[1], r1 = std::max(R, 1), u1 = std::max(U, 1);
+        if (small ? R == 0 : R > 0) continue;
+        if ((R == 4 && P.w > 2) || (R == 2 && P.w > 5) || (R == 1 && U == 2 && P.w > 10)) continue;
+        if (U > 1 && !reads_inside(P, P.conv, U - 1)) continue;
+        int last_B = 0;
+        for (long budget : {98304L, 49152L, 24576L}) {
+            const int B = (int)std::min<long>(std::max(Lmax, 2), (budget - (long)sizeof(JobOffsets) * Lmax) /
+                                                                     ((long)(P.d + 1) * P.w * 8));
+            const long lds = chain_lds_bytes(P.d + 1, P.w, u1, B, 2 * Lmax);
+            if (B == last_B) continue;
+            last_B = B;
+            if (B < 2 || lds > kMaxLdsBytes || (budget < 98304 && chains.size() <= (size_t)kSimds / 4)) break;
+            for (int W : {1, 2, 4, 8, 12, 16}) {
+                // up to 16 wavefronts (1024 threads, 128 VGPRs each) where that
+                // needs no spills; one or two only for many chains
+                if ((W > 8 && P.w * u1 > 10) || (W == 16 && P.w > 8)) continue;
+                if (W < 4 && (R == 0 || chains.size() < 64)) continue;
+                for (int S : {1, 2}) {
+                    if (W == 1 && S > 1) continue;
+                    // (not worth a schedule if its fewest iterations cost more than the best)
+                    const int items = P.d / r1, tail = R == 1 ? P.d / u1 + 1 : items + 1;
+                    const long all = R == 1 ? (long)tail * (P.d + 1 - (tail - 1) * (long)u1 / 2) : (long)tail * (tail + 1) / 2;
+                    const int fewest = (int)std::max(Lmax * all / (kLanes * W), (long)Lmax - 1 + tail);
+                    if (best >= 0 && chain_cost(P, chains.size(), r1, u1, W, S, fewest, lds) >= best) continue;
+                    std::vector<int32_t> cs;
+                    int stride = 0;
+                    const int steps = make_chain_schedule(Lmax, P.d / r1, W, S, B, cs, &stride, R == 1 ? U : 1);
+                    const double c = chain_cost(P, chains.size(), r1, u1, W, S, steps, lds);
+                    if (best < 0 || c < best) {
+                        best = c;
+                        br = R;
+                        bu = U;
+                        bw = W;
+                        bs = S;
+                        bb = B;
+                    }
+                }
             }
         }
-    if (best < 0 || (!forced && best >= 0.9 * other)) return false;
-    return make_chain_plan(P, chains, bw, bs, B) >= 0;
+    }
+    if (best < 0 || !make_chain_plan(P, chains, br, bu, bw, bs, bb)) return false;
+    const double rest = layers_cost(P, P.pipe_layers + 1);
+    return forced || best + rest < 0.9 * other;
 }
 
 // ----------------------------------------------------------- single launch
@@ -950,18 +1144,8 @@ static std::string build_plan_launches(int n, int N, int d, int m, const int32_t
     // so b_{n-2} must stay readable while b_{n-2} * a_k is stored.
     const bool chain_forced = (flags & kChainLaunch) != 0;
     if (!P.streamed && !(flags & (kFusedLayers | kLayerLaunches | kNoChainLaunch)) &&
-        (chain_forced || (kChainByDefault && P.n_layers() >= 16))) {
-        // the plan without it, in the layer cost model's units: dealt steps
-        // weigh what choose_staged_lanes gives them
-        const int Q = P.lanes.waves_per_job, J = P.lanes.jobs_per_group;
-        double other = P.simple ? layer_cost(P, Q, J, dealt_steps(d, J, Q), P.w == 1 ? 0.15 : 0.4)
-                                : layer_cost(P, Q, J, P.lanes.steps, 1.0);
-        if (fuse_by_default(P)) {
-            const LaneSchedule one = make_lane_schedule(d, 1);
-            const double per = prefer_simple_dealing(d, 1, P.w, one.steps) ? dealt_steps(d, 1) * (P.w == 1 ? 0.15 : 0.5)
-                                                                           : (double)one.steps;
-            other = std::min(other, P.n_layers() * per);
-        }
+        (chain_forced || P.n_layers() >= 9)) {
+        const double other = layers_cost(P, 1);
         Plan C;
         bool uns = false;
         std::string e2 = build_plan_mode(n, N, d, m, nvars, vars, exps, flags, false, true, C, &uns);
@@ -1292,24 +1476,34 @@ static std::string build_plan_mode(int n, int N, int d, int m, const int32_t *nv
             for (const auto &t : P.conv) inplace |= t[0] == t[2];
             if (inplace) return build_plan_mode(n, N, d, m, nvars, vars, exps, flags, false, true, P, unsupported);
         }
+        choose_block_lanes(P, 1);
     }
     // after the lane choice: the check depends on the wavefronts per job
     auto err = check_hazards(P);
     if (!err.empty()) return "internal planner error: " + err;
     if (!(flags & kAsapLayers)) {
-        const int J = P.lanes.jobs_per_group, Q = P.lanes.waves_per_job;
-        const double before = layer_cost(P, Q, J, P.lanes.steps, 1.0);
-        auto conv = P.conv;
-        auto off = P.conv_off;
-        if (balance_layers(P, std::max(1L, kSimds * J / Q))) {
-            if (layer_cost(P, Q, J, P.lanes.steps, 1.0) < before) {
+        // whole rounds of the coefficient schedule's wavefronts, and, where the
+        // launches run blocks, of the blocks' wavefronts too
+        auto cost = [&](const LaneSchedule &ls) {
+            return layer_cost(P, ls.waves_per_job, ls.jobs_per_group, ls.steps, 1.0);
+        };
+        auto balance = [&](const LaneSchedule &round, const LaneSchedule &by) {
+            const double before = cost(by);
+            auto conv = P.conv;
+            auto off = P.conv_off;
+            if (!balance_layers(P, std::max(1L, kSimds * round.jobs_per_group / round.waves_per_job))) return;
+            if (cost(by) < before) {
                 P.balanced = true;
-                auto e = check_hazards(P);
-                if (!e.empty()) return "internal planner error after layer balancing: " + e;
             } else {
                 P.conv.swap(conv);
                 P.conv_off.swap(off);
             }
+        };
+        balance(P.lanes, P.lanes);
+        if (P.block_r > 0) balance(P.blocks, P.blocks);
+        if (P.balanced) {
+            auto e = check_hazards(P);
+            if (!e.empty()) return "internal planner error after layer balancing: " + e;
         }
     }
     return "";

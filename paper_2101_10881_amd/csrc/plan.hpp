@@ -51,6 +51,30 @@ __host__ __device__ inline long group_lds_bytes(long d1, int doubles_per_coef, i
     return conv_lds_jobs_offset((long)J * d1 * doubles_per_coef) + (long)J * (long)sizeof(JobOffsets);
 }
 
+// LDS layout of one wavefront's group of the blocked convolution (blocks of R
+// coefficients per lane, conv_block.hpp): a front pad, X[J] series, Y[J]
+// series (only when stages_second_operand(W)), an end pad of one block, then
+// the J JobOffsets.  The pads hold what a top block reads past an operand.  A
+// job's series start 2 doubles past a multiple of 32 (the 64 LDS banks), so
+// that lanes of different jobs at one coefficient read different banks.
+__host__ __device__ constexpr int block_front_pad(int w, int U) { return (U * w + 1) / 2 * 2; }
+__host__ __device__ inline int block_series_stride(int d1, int w) { return (d1 * w + 31) / 32 * 32 + 2; }
+__host__ __device__ inline long block_jobs_offset(int d1, int w, int U, int J) {  // in doubles
+    return 2L * block_front_pad(w, U) + (long)J * (stages_second_operand(w) ? 2 : 1) * block_series_stride(d1, w);
+}
+__host__ __device__ inline long block_group_bytes(int d1, int w, int U, int J) {
+    return block_jobs_offset(d1, w, U, J) * 8 + (long)J * 16;  // BlockJob
+}
+
+// LDS doubles of one first operand of the blocked chain launch: whole blocks.
+__host__ __device__ constexpr int chain_slot_doubles(int d1, int w, int R) {
+    return ((d1 + R - 1) / R * R * w + 1) / 2 * 2;
+}
+// LDS of a chain: B slots, one for the last job's blocks, the jobs' offsets.
+__host__ __device__ constexpr long chain_lds_bytes(int d1, int w, int R, int B, int jobs) {
+    return (B + 1L) * chain_slot_doubles(d1, w, R) * 8 + 16L * jobs;
+}
+
 constexpr uint32_t kKeepMonomialValues = 1u;
 constexpr uint32_t kComplex = 2u;          // complex series: real limbs, then imaginary limbs
 constexpr uint32_t kStreamOperands = 4u;   // read both convolution operands from global memory
@@ -92,6 +116,11 @@ struct Plan {
     // coefficient, run after the last convolution layer, before the additions
     std::vector<std::array<int32_t, 3>> scale;
     LaneSchedule lanes;
+    // blocked convolutions (staged operands): the lane schedule of blocks of
+    // block_r coefficients that the per-layer launches and the reverse pass
+    // run (block_r = 0: the schedule `lanes`, coefficient by coefficient)
+    int block_r = 0, block_u = 0;
+    LaneSchedule blocks;
     // addition trees: the slots of each output's list (the value's, then each
     // derivative's) in tree order; list o spans list_slots[list_off[o] .. list_off[o+1])
     std::vector<int32_t> list_slots;
@@ -125,6 +154,9 @@ struct Plan {
     int32_t fused_waves = 0;
     LaneSchedule fused_lanes;
     bool fused_simple = false;
+    // the fused launch by blocks: wavefronts of a workgroup (0: by coefficients) and the schedule
+    int32_t fused_block_waves = 0;
+    LaneSchedule fused_blocks;
     // Chain launch (kChainLaunch, or chosen by the cost model): chains of
     // convolutions where each job's first operand is the previous job's
     // output and its second a staged input series (p2's forward and backward
@@ -143,7 +175,10 @@ struct Plan {
     // for g idle steps, then -1.
     // pipe_ring: LDS slots of first operands per chain (job j's in slot j mod pipe_ring).
     int pipe_layers = 0;
-    int pipe_waves = 0, pipe_window = 0, pipe_ring = 0;
+    // pipe_r > 0: by blocks of pipe_r coefficients, pipe_u terms an iteration
+    // (chain.hip), block codes and iterations in place of coefficient codes and
+    // steps.
+    int pipe_waves = 0, pipe_window = 0, pipe_ring = 0, pipe_r = 0, pipe_u = 0;
     std::vector<std::array<int32_t, 3>> pipe_jobs;
     std::vector<ChainComp> pipe_comps;
     std::vector<int32_t> pipe_codes;
@@ -167,6 +202,9 @@ std::string build_plan(int n, int N, int d, int m, const int32_t *nvars, const i
                        uint32_t flags, Plan &out, bool *unsupported);
 
 LaneSchedule make_lane_schedule(int d, int jobs_per_group, int waves_per_job = 1);
+// The blocked convolution's schedule: items of R coefficients, U terms an
+// iteration (R = 1, or R = U), `steps` in iterations.
+LaneSchedule make_block_schedule(int d, int R, int U, int J, int Q);
 LaneSchedule make_paired_schedule(int d, int waves_per_job);
 // Streamed operands: wavefronts per job for degree d, and whether the paired
 // schedule is used (large d, where first-fit would be slow to build).
@@ -196,6 +234,13 @@ struct AddPasses {
 // level-by-level additions leave it, in its last leaf's slot, and the next
 // pass runs over those slots.
 AddPasses make_add_passes(const Plan &P, int cover);
+// The independent component of every convolution job; returns their number.
+int32_t job_components(const Plan &P, std::vector<int32_t> &comp);
+// What the blocked kernels need of a plan: 32-bit byte offsets into its
+// workspace, and that `over` coefficients before and past every job's second
+// operand lie inside it.
+bool small_workspace(const Plan &P);
+bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs, int over);
 // The rules every plan meets (Section 5: the jobs of one layer are
 // independent): a job reads only slots written at an earlier stage (inputs,
 // an earlier layer or level); no two jobs of a stage write one slot, and no
@@ -209,7 +254,9 @@ std::string check_hazards(const Plan &P);
 // with a workgroup barrier every S steps and first operands in B LDS slots:
 // codes (64W rows of *stride entries, the encoding of Plan::pipe_codes).
 // Returns the steps (an even multiple of S).
-int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> &codes, int *stride);
+// With U > 1 a coefficient's terms are taken U an iteration: coefficient k
+// takes k / U + 1 iterations and reads x_i one iteration before its i / U-th.
+int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> &codes, int *stride, int U = 1);
 // Checks a chain schedule against the kernel's timing: every coefficient of
 // every job exactly once, within `steps`; the first operand of step t is read
 // from LDS in iteration t-1 (the prologue, iteration -1, for step 0), a
@@ -218,6 +265,7 @@ int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> 
 // job's first operand must come after the barrier that follows the store of
 // that coefficient by the previous job, and before the barrier that precedes
 // its overwriting (B slots later).  Returns "" or what is wrong.
-std::string check_chain_schedule(int L, int d, int W, int S, int B, int steps, const int32_t *codes, int stride);
+std::string check_chain_schedule(int L, int d, int W, int S, int B, int steps, const int32_t *codes, int stride,
+                                 int U = 1);
 
 }  // namespace mdpe

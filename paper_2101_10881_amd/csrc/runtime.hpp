@@ -17,6 +17,7 @@ constexpr int kMaxDevices = 64;
 struct mdpe_plan {
     mdpe::Plan P;
     int device = -1;
+    void *d_arena = nullptr;   // the one device allocation that holds the arrays below
     int4 *d_conv = nullptr;
     int2 *d_add = nullptr;
     int2 *d_stage = nullptr;
@@ -35,6 +36,8 @@ struct mdpe_plan {
     int *d_pcodes = nullptr;   // chain launch: lane schedules
     int *d_coff = nullptr;     // single launch: convolution layer offsets (int32)
     int *d_aoff = nullptr;     // single launch: addition level offsets (int32)
+    int *d_blocks = nullptr;   // blocked convolutions: their lane schedule
+    int *d_fblocks = nullptr;  // fused blocked convolutions: their lane schedule
     int *d_leaves = nullptr;   // addition passes: list slots
     mdpe::AddChunk *d_chunks = nullptr;  // addition passes: workgroups' parts
     std::vector<int64_t> add_pass;       // pass p spans d_chunks[add_pass[p] .. add_pass[p+1])
@@ -44,10 +47,17 @@ struct mdpe_plan {
 // launchers of the other translation units (each returns an MDPE_* status and
 // leaves its message for last_error_string)
 namespace mdpe {
+// One layer of jobs as blocked convolutions (block_r > 0) on `st`.
+int launch_block_layer(const mdpe_plan *pl, bool corr, double *A, const int4 *jobs, int nj, hipStream_t st);
+// Every layer in one launch as blocked convolutions (fused_block_waves > 0).
+int launch_block_fused(const mdpe_plan *pl, double *A, hipStream_t st);
+// The chain launch by blocks (pipe_r > 0).
+int launch_block_chain(const mdpe_plan *pl, double *A, hipStream_t st);
 // Pass p of the plan's addition trees; the last pass of a list writes the
 // caller's value or gradient.
 int launch_add_pass(const mdpe_plan *pl, int p, double *A, double *value, double *grad, hipStream_t st);
 int add_pass_cover(int w);  // leaves of one workgroup's part
+int simd_count(int device);
 }  // namespace mdpe
 
 namespace mdpe {
