@@ -78,7 +78,7 @@ struct BatchTask {
 constexpr int kSpinLimit = 1 << 22;
 constexpr int kQueues = 8;  // one task queue per XCD
 constexpr int kSummed = -2;
-constexpr int kSetComponents = 512;  // resident wavefronts of an XCD (32 CUs x 16)
+constexpr int kSetComponents = 256;  // resident wavefronts of an XCD (32 CUs x 8)
 
 // the XCD (XCC) this wavefront runs on
 __device__ __forceinline__ int xcd_id() { return (int)(__builtin_amdgcn_s_getreg(20 | (15 << 11)) & (kQueues - 1)); }
@@ -411,6 +411,12 @@ int prepare_batch(mdpe_batch *b) {
         // SIMDs get equal numbers (17 resident per CU put five on one SIMD,
         // whose tasks ran slowest: 16 measured 0.6% faster on the mixed batch)
         if (per_cu > 4) per_cu -= per_cu % 4;
+        // Blocked convolutions keep a SIMD busy with few wavefronts, and with
+        // fewer of them every task, and so the launch's last ones, end sooner.
+        // 2, 3 and 4 per SIMD measured (ms): 64 mixed instances 6.19, 8.20,
+        // 8.10; 128 7.72, 8.36, 8.35; 256 17.2, 17.1, 17.0; 512 (64837
+        // convolution tasks) 29.1, 27.2, 28.1.
+        if (BLK) per_cu = std::min(per_cu, b->stage_tasks[1] >= 40000 ? 12 : 8);
         b->grid = std::max(1, per_cu) * cus;
     }
     return MDPE_OK;
@@ -738,7 +744,7 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         B->inst_queue[p] = best;
     }
     // Convolutions by component sets where a queue has a component for every
-    // resident wavefront of its XCD (32 CUs x 16): a task then runs whole
+    // resident wavefront of its XCD (32 CUs x 8): a task then runs whole
     // components (monomials), its groups one after the other on one wavefront,
     // and no convolution waits for another task -- one stage instead of a
     // layer's after layer's, each with its release, acquire and idle
