@@ -83,8 +83,10 @@ constexpr int kSetComponents = 256;  // resident wavefronts of an XCD (32 CUs x 
 // the XCD (XCC) this wavefront runs on
 __device__ __forceinline__ int xcd_id() { return (int)(__builtin_amdgcn_s_getreg(20 | (15 << 11)) & (kQueues - 1)); }
 
-// Terms an iteration of the blocked convolutions takes at width w.
-__host__ __device__ constexpr int batch_terms(int w) { return w <= 2 ? 4 : 2; }
+// Terms an iteration of the blocked convolutions takes at width w (four against
+// two at three doubles 1.05 times as fast, 64 instances at d = 50; at four
+// doubles 0.98 to 1.02, so two there).
+__host__ __device__ constexpr int batch_terms(int w) { return w <= 3 ? 4 : 2; }
 
 // An addition task by passes: each lane sums one part of an output's list (up to
 // add_pass_cover leaves) at one coefficient, E elements at a time with their
@@ -152,17 +154,31 @@ __device__ void run_task(const BatchTask &T, const BatchInst &I, double *lds, in
             // a set's groups one after the other (the barrier orders a group's
             // stores before the next one's loads), or a run of one layer's jobs
             const int groups = T.groups > 0 ? T.groups : (T.count + I.J - 1) / I.J;
-            for (int g = 0; g < groups; ++g) {
-                long a = T.first + (long)g * I.J;
-                int jn = min(I.J, T.count - g * I.J);
+            auto range = [&](int g, long &a, int &jn) {
+                a = T.first + (long)g * I.J;
+                jn = min(I.J, T.count - g * I.J);
                 if (T.groups > 0) {
                     a = I.goff[T.group + g];
                     jn = I.goff[T.group + g + 1] - (int)a;
                 }
-                conv_block_group<M, false, false, 1, batch_terms(M)>(I.A, I.conv + a, __builtin_amdgcn_readfirstlane(jn),
-                                                                     I.J, I.d, lds, I.chains, I.stride, I.steps, lane,
-                                                                     lane);
+            };
+            long a;
+            int jn;
+            range(0, a, jn);
+            int4 job = lane < jn ? I.conv[a + lane] : make_int4(0, 0, 0, 0);
+            for (int g = 0; g < groups; ++g) {
+                // the next group's jobs load while this one's run
+                int jn2 = 0;
+                int4 job2 = make_int4(0, 0, 0, 0);
+                if (g + 1 < groups) {
+                    range(g + 1, a, jn2);
+                    if (lane < jn2) job2 = I.conv[a + lane];
+                }
+                conv_block_group<M, false, false, 1, batch_terms(M)>(I.A, job, __builtin_amdgcn_readfirstlane(jn), I.J,
+                                                                     I.d, lds, I.chains, I.stride, I.steps, lane, lane);
                 __syncthreads();
+                jn = jn2;
+                job = job2;
             }
         } else {
             for (int g = 0; g < T.count; g += I.J) {
@@ -691,15 +707,16 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
     };
     // Convolutions by blocks at two to five doubles per coefficient, where
     // every instance meets what the blocked kernel needs (32-bit offsets;
-    // second operands read from global memory not at the workspace's ends;
-    // a group's padded operands in LDS)
+    // second operands read from global memory not at the workspace's start;
+    // a group's padded operands in LDS, its descriptors one per lane)
     B->blocks = ms[0] >= 2 && ms.back() <= 5;
     for (int p = 0; p < count && B->blocks; ++p) {
         const mdpe::Plan &P = plans[p]->P;
-        B->blocks = mdpe::block_group_bytes(P.d + 1, P.m, mdpe::batch_terms(P.m), tile_for(P.m, P.d).jobs_per_group) <=
+        const int J = tile_for(P.m, P.d).jobs_per_group;
+        B->blocks = J <= mdpe::kLanes && mdpe::block_group_bytes(P.d + 1, P.m, mdpe::batch_terms(P.m), J) <=
                         mdpe::kMaxLdsBytes &&
                     mdpe::small_workspace(P) &&
-                    (mdpe::stages_second_operand(P.m) || mdpe::reads_inside(P, P.conv, mdpe::batch_terms(P.m) - 1));
+                    (mdpe::stages_second_operand(P.m) || mdpe::reads_inside(P, P.conv, mdpe::batch_terms(P.m) - 1, 0));
     }
     // schedules per (d, J, terms an iteration)
     std::map<std::array<int, 3>, int> sched_index;

@@ -19,8 +19,9 @@ __global__ __launch_bounds__(64 * WPB) void conv_block_kernel(double *__restrict
     const int g = Q == 1 ? wv : wv / Q;
     const int part = wv - g * Q;
     const int lane = threadIdx.x & 63;
-    const int g0 = min(g * J, njobs);
-    conv_block_group<M, CORR, CX, R, U>(A, jobs + g0, min(J, njobs - g0), J, d,
+    const int g0 = min(g * J, njobs), jn = min(J, njobs - g0);
+    const int4 job = lane < jn ? jobs[g0 + lane] : make_int4(0, 0, 0, 0);
+    conv_block_group<M, CORR, CX, R, U>(A, job, jn, J, d,
                                      (double *)((char *)lds + wave * group_bytes), chains, stride, its, lane,
                                      part * 64 + lane);
 }
@@ -40,15 +41,24 @@ __global__ __launch_bounds__(64 * WAVES) void conv_fused_block_kernel(double *__
     const int waves = (int)(blockDim.x >> 6), wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
     const int *o = off + (long)blockIdx.x * (nl + 1);
     double *mine = (double *)((char *)lds + wave * group_bytes);
-    for (int L = 0; L < nl; ++L) {
-        const int a = o[L], b = o[L + 1];
-        for (int r = a; r < b; r += waves * J) {
-            const int q = r + wave * J;
-            const int jn = q < b ? min(J, b - q) : 0;
-            conv_block_group<M, false, CX, 1, U>(A, jobs + (jn > 0 ? q : a), jn, J, d, mine, chains, stride, its, lane,
-                                                 lane);
-        }
-        __syncthreads();
+    // this wavefront's next jobs are loaded a round ahead
+    int L = 0, r = o[0] + wave * J;
+    auto jobs_left = [&](int at, int end) { return max(0, min(J, end - at)); };
+    int jn = jobs_left(r, o[1]);
+    int4 job = lane < jn ? jobs[r + lane] : make_int4(0, 0, 0, 0);
+    while (L < nl) {
+        // every wavefront of the workgroup moves on by the same rule
+        const int end = o[L + 1];
+        const bool layer_ends = r - wave * J + waves * J >= end;
+        const int L2 = layer_ends ? L + 1 : L, r2 = layer_ends ? end + wave * J : r + waves * J;
+        const int jn2 = L2 < nl ? jobs_left(r2, o[L2 + 1]) : 0;
+        const int4 job2 = lane < jn2 ? jobs[r2 + lane] : make_int4(0, 0, 0, 0);
+        conv_block_group<M, false, CX, 1, U>(A, job, jn, J, d, mine, chains, stride, its, lane, lane);
+        if (layer_ends) __syncthreads();
+        L = L2;
+        r = r2;
+        jn = jn2;
+        job = job2;
     }
 }
 
@@ -90,9 +100,9 @@ int launch_r(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipStream
     return MDPE_OK;
 }
 
-template <int M, bool CX, int WAVES>
+template <int M, bool CX, int U, int WAVES>
 int launch_fused_w(const mdpe_plan *pl, double *A, hipStream_t st) {
-    constexpr int W = kCoef<M, CX>, U = W <= 2 ? 4 : 2;
+    constexpr int W = kCoef<M, CX>;
     const Plan &P = pl->P;
     const LaneSchedule &ls = P.fused_blocks;
     const int J = ls.jobs_per_group, waves = P.fused_block_waves;
@@ -113,11 +123,24 @@ int launch_fused_w(const mdpe_plan *pl, double *A, hipStream_t st) {
     return MDPE_OK;
 }
 
-template <int M>
+template <int M, bool CX, int U>
+int launch_fused_u(const mdpe_plan *pl, double *A, hipStream_t st) {
+    if (pl->P.fused_block_waves == 1) return launch_fused_w<M, CX, U, 1>(pl, A, st);
+    return launch_fused_w<M, CX, U, 4>(pl, A, st);
+}
+
+template <int M, bool CX>
 int launch_fused_m(const mdpe_plan *pl, double *A, hipStream_t st) {
-    if (pl->P.fused_block_waves == 1)
-        return pl->P.complex_series() ? launch_fused_w<M, true, 1>(pl, A, st) : launch_fused_w<M, false, 1>(pl, A, st);
-    return pl->P.complex_series() ? launch_fused_w<M, true, 4>(pl, A, st) : launch_fused_w<M, false, 4>(pl, A, st);
+    if constexpr (kCoef<M, CX> <= 5) {
+        if (block_terms_of(pl->P.w, pl->P.d) == 4) return launch_fused_u<M, CX, 4>(pl, A, st);
+        if constexpr (kCoef<M, CX> > 2) return launch_fused_u<M, CX, 2>(pl, A, st);
+    }
+    return fail(MDPE_EUNSUPPORTED, "no fused blocked convolution of this width");
+}
+
+template <int M>
+int launch_fused_f(const mdpe_plan *pl, double *A, hipStream_t st) {
+    return pl->P.complex_series() ? launch_fused_m<M, true>(pl, A, st) : launch_fused_m<M, false>(pl, A, st);
 }
 
 template <int M, bool CORR, bool CX>
@@ -126,11 +149,10 @@ int launch_m(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipStream
     const int ru = 10 * pl->P.block_r + pl->P.block_u;
     if constexpr (W == 1)
         if (ru == 44) return launch_r<M, CORR, CX, 4, 4>(pl, A, jobs, nj, st);
-    if constexpr (W <= 2) {
+    if constexpr (W <= 5)
         if (ru == 14) return launch_r<M, CORR, CX, 1, 4>(pl, A, jobs, nj, st);
-    } else {
+    if constexpr (W > 2)
         if (ru == 12) return launch_r<M, CORR, CX, 1, 2>(pl, A, jobs, nj, st);
-    }
     return fail(MDPE_EUNSUPPORTED, "no blocked convolution of this width");
 }
 
@@ -145,11 +167,11 @@ int launch_f(const mdpe_plan *pl, bool corr, double *A, const int4 *jobs, int nj
 
 int launch_block_fused(const mdpe_plan *pl, double *A, hipStream_t st) {
     switch (pl->P.m) {
-        case 1: return launch_fused_m<1>(pl, A, st);
-        case 2: return launch_fused_m<2>(pl, A, st);
-        case 3: return launch_fused_m<3>(pl, A, st);
-        case 4: return launch_fused_m<4>(pl, A, st);
-        case 5: return launch_fused_m<5>(pl, A, st);
+        case 1: return launch_fused_f<1>(pl, A, st);
+        case 2: return launch_fused_f<2>(pl, A, st);
+        case 3: return launch_fused_f<3>(pl, A, st);
+        case 4: return launch_fused_f<4>(pl, A, st);
+        case 5: return launch_fused_f<5>(pl, A, st);
         default: return fail(MDPE_EUNSUPPORTED, "no fused blocked convolution of this width");
     }
 }

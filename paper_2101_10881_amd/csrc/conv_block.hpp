@@ -147,21 +147,21 @@ __device__ __forceinline__ void block_terms(double (&cur)[U][W], double (&x)[U][
     }
 }
 
-// Descriptors, then the staged operands of jobs[0..jn) as one flat range with
-// several loads in flight per lane: the first operand, which may be the job's
-// own output, and for coefficients of at most two doubles the second too.
+// Descriptors (lane j holds job j's), then the staged operands of the jn jobs as
+// one flat range with several loads in flight per lane: the first operand, which
+// may be the job's own output, and for coefficients of at most two doubles the
+// second too.
 template <int M, bool CORR, bool CX, int U>
-__device__ __forceinline__ void block_stage(const double *__restrict__ A, const int4 *__restrict__ jobs, int jn, int J,
-                                            int d, double *lds, int lane) {
+__device__ __forceinline__ void block_stage(const double *__restrict__ A, int4 job, int jn, int J, int d, double *lds,
+                                            int lane) {
     constexpr int W = kCoef<M, CX>;
     constexpr bool YL = stages_second_operand(W);
     const int S = (d + 1) * W, SX = block_series_stride(d + 1, W);
     double *X = lds + block_front_pad(W, U), *Y = X + (long)J * SX;
     BlockJob *jd = (BlockJob *)(lds + block_jobs_offset(d + 1, W, U, J));
-    for (int j = lane; j < jn; j += 64) {
-        const int4 t = jobs[j];
+    if (lane < jn) {
         const unsigned S8 = (unsigned)S * 8u;
-        jd[j] = BlockJob{(unsigned)t.x * S8, (unsigned)t.y * S8, (unsigned)t.z * S8, 0u};
+        jd[lane] = BlockJob{(unsigned)job.x * S8, (unsigned)job.y * S8, (unsigned)job.z * S8, 0u};
     }
     __syncthreads();
     const int total = jn * S;
@@ -197,17 +197,20 @@ __device__ __forceinline__ void block_stage(const double *__restrict__ A, const 
     __syncthreads();
 }
 
-// One wavefront's group: jn <= J jobs, the lanes' items from the schedule
-// `chains` (code (job << 16) | item, -1 after a row's last), `its` iterations.
+// One wavefront's group: jn <= J <= 64 jobs (lane j holds job j's {t1, t2, t3}, so
+// that a caller with several groups can load the next one's early), the lanes'
+// items from the schedule `chains` (code (job << 16) | item, -1 after a row's
+// last), `its` iterations.
 // lds: block_group_bytes(d + 1, W, U, J).  Ends with the wavefront's stores
 // issued.  Reads past a series only enter terms or coefficients that are
 // dropped: in LDS up to one block past either end of an operand (padded); in
-// global memory at most U - 1 coefficients past or before the second operand's
-// slot, inside the workspace (the host checks that).
+// global memory at most U - 1 coefficients before (convolution, R = 1) or past
+// (R > 1, reverse pass) the second operand's slot, inside the workspace (the host
+// checks that: reads_inside).
 template <int M, bool CORR, bool CX, int R, int U>
-__device__ __forceinline__ void conv_block_group(double *__restrict__ A, const int4 *__restrict__ jobs, int jn, int J,
-                                                 int d, double *lds, const int *__restrict__ chains, int stride,
-                                                 int its, int lane, int row) {
+__device__ __forceinline__ void conv_block_group(double *__restrict__ A, int4 job, int jn, int J, int d, double *lds,
+                                                 const int *__restrict__ chains, int stride, int its, int lane,
+                                                 int row) {
     constexpr int W = kCoef<M, CX>, W8 = 8 * W;
     static_assert(R == 1 || R == U, "one coefficient, or square tiles");
     constexpr bool YL = stages_second_operand(W);
@@ -228,7 +231,7 @@ __device__ __forceinline__ void conv_block_group(double *__restrict__ A, const i
     const int c0 = next_code(), c1 = next_code();
     int c2 = next_code(), c3 = next_code();
 
-    block_stage<M, CORR, CX, U>(A, jobs, jn, J, d, lds, lane);
+    block_stage<M, CORR, CX, U>(A, job, jn, J, d, lds, lane);
     if (jn <= 0) return;  // a wavefront past the last group (after the workgroup barriers)
 
     auto job_of = [&](int c) { return c >= 0 && (c >> 16) < jn ? c >> 16 : 0; };

@@ -387,11 +387,11 @@ bool small_workspace(const Plan &P) {
     return P.n_series * (int64_t)(P.d + 1) * P.w * 8 <= 0xffff0000LL;
 }
 
-// Whether reading `over` coefficients before and past the second operand of
-// every job stays inside the workspace.
-bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs, int over) {
+// Whether reading `before` and `past` coefficients before and past the second
+// operand of every job stays inside the workspace.
+bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs, int before, int past) {
     for (const auto &t : jobs)
-        if ((int64_t)t[1] * (P.d + 1) < over || (P.n_series - 1 - t[1]) * (int64_t)(P.d + 1) < over) return false;
+        if ((int64_t)t[1] * (P.d + 1) < before || (P.n_series - 1 - t[1]) * (int64_t)(P.d + 1) < past) return false;
     return true;
 }
 
@@ -413,13 +413,23 @@ static bool blocks_pay(const Plan &P) {
     return P.d >= 128 || most > 6144;
 }
 
+// Terms an iteration of the blocked per-layer and fused launches takes: four
+// keep more independent products in flight, but an item's last iteration is
+// padded to them.  Four against two (p1 / p3, wall time): three doubles per
+// coefficient 0.97 times as fast at d = 8, 0.98 at 12, 1.00 at 16, 1.04 at 24,
+// 1.10 at 31, 1.05 at 63 and 152; four 0.95 at d = 8, 0.97 at 20, 1.01 at 24,
+// 1.05 at 31, 1.03 at 63, 1.22 on p3's d = 120; five 0.95, 0.99, 1.02, 1.00,
+// 1.02, with exponents 1.11.  Up to two doubles always four (six and eight: 0.92
+// to 1.06).
+int block_terms_of(int w, int d) { return w <= 2 || (w <= 5 && d >= 24) ? 4 : 2; }
+
 // Blocks of R coefficients per lane, U terms an iteration, for the staged
 // per-layer launches (conv_block.hpp) of the layers from_layer..., J jobs per
 // wavefront and Q wavefronts per job, by the estimated cycles of the layers.
-// One coefficient and four terms at up to two doubles per coefficient, two
-// terms beyond (four coefficients and terms too at one double, where loads
-// count: p1 d = 152 1.13 against 0.94 times the other kernel's speed; tiles of
-// 2 x 2 measured slower nearly everywhere: they halve the wavefronts).
+// One coefficient and block_terms_of terms; four coefficients and terms too at
+// one double, where loads count (p1 d = 152: 1.13 against 0.94 times the other
+// kernel's speed).  Tiles of 2 x 2 measured 0.74 to 0.98 on p1 at three and four
+// doubles, 1.07 at best (p3): they halve the wavefronts.
 static void choose_block_lanes(Plan &P, int from_layer) {
     P.block_r = P.block_u = 0;
     P.blocks = LaneSchedule();
@@ -428,11 +438,14 @@ static void choose_block_lanes(Plan &P, int from_layer) {
     const int maxq = P.lanes.waves_per_job > 1 ? 4 : 1;
     double best = -1;
     for (int R : {1, 4}) {
-        const int U = w <= 2 ? 4 : 2;
+        const int U = block_terms_of(w, P.d);
         if (R == 4 && w > 1) continue;
         // second operands in global memory are read up to U - 1 coefficients
-        // past either end
-        if (!stages_second_operand(w) && !(reads_inside(P, P.conv, U - 1) && reads_inside(P, P.corr, U - 1))) continue;
+        // before (one coefficient's terms, going down) or past their slot
+        // (blocks of R; the reverse pass's shared operand)
+        if (!stages_second_operand(w) && !(reads_inside(P, P.conv, R == 1 ? U - 1 : 0, R == 1 ? 0 : U - 1) &&
+                                           reads_inside(P, P.corr, 0, U - 1)))
+            continue;
         const long longest = P.d / U + 1, items = P.d / R + 1;
         for (int J : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64}) {
             if (block_group_bytes(P.d + 1, w, U, J) > kLdsBudget && J > 1) break;
@@ -460,8 +473,8 @@ static void choose_fused_blocks(Plan &P, int widest) {
     // fast at d = 8, 1.21 at d = 31, 0.95 at d = 63; one double 0.57 to 0.9; 210
     // products of four of ten variables at three to five doubles 1.10 to 1.18
     if (P.w == 1 || P.w > 5 || (P.w == 2 && P.d > 40) || !blocks_pay(P) || widest < 1) return;
-    const int U = P.w <= 2 ? 4 : 2;
-    if (!stages_second_operand(P.w) && !reads_inside(P, P.conv, U - 1)) return;
+    const int U = block_terms_of(P.w, P.d);
+    if (!stages_second_operand(P.w) && !reads_inside(P, P.conv, U - 1, 0)) return;
     double best = -1;
     for (int waves = 1; waves <= 4; ++waves) {
         const int J = std::min((widest + waves - 1) / waves, 16);
@@ -984,12 +997,13 @@ static bool choose_chain_launch(Plan &P, bool forced, double other) {
     int br = 0, bu = 0, bw = 0, bs = 0, bb = 0;
     // by coefficients (R = 0, the 64-bit addresses) where the workspace is 4 GiB or more
     const bool small = small_workspace(P);
+    // (four terms of one coefficient: 0.63 to 1.0 on p2, 1.05 at best)
     static const int kRU[5][2] = {{0, 0}, {1, 1}, {1, 2}, {2, 2}, {4, 4}};
     for (auto &ru : kRU) {
         const int R = ru[0], U = ru[1], r1 = std::max(R, 1), u1 = std::max(U, 1);
         if (small ? R == 0 : R > 0) continue;
         if ((R == 4 && P.w > 2) || (R == 2 && P.w > 5) || (R == 1 && U == 2 && P.w > 10)) continue;
-        if (U > 1 && !reads_inside(P, P.conv, U - 1)) continue;
+        if (U > 1 && !reads_inside(P, P.conv, R == 1 ? U - 1 : 0, R == 1 ? 0 : U - 1)) continue;
         int last_B = 0;
         for (long budget : {98304L, 49152L, 24576L}) {
             const int B = (int)std::min<long>(std::max(Lmax, 2), (budget - (long)sizeof(JobOffsets) * Lmax) /
@@ -1143,8 +1157,17 @@ static std::string build_plan_launches(int n, int N, int d, int m, const int32_t
     // the in-place products fresh output slots: a chain's products overlap,
     // so b_{n-2} must stay readable while b_{n-2} * a_k is stored.
     const bool chain_forced = (flags & kChainLaunch) != 0;
+    // (a chain of nine products takes a monomial of at least seven variables, or
+    // a power table that long: no second plan is built for less)
+    int longest = 0;
+    int64_t at = 0;
+    for (int k = 0; k < N; ++k) {
+        longest = std::max(longest, nvars[k] + 2);
+        for (int q = 0; q < nvars[k]; ++q, ++at)
+            if (exps) longest = std::max(longest, exps[at]);
+    }
     if (!P.streamed && !(flags & (kFusedLayers | kLayerLaunches | kNoChainLaunch)) &&
-        (chain_forced || P.n_layers() >= 9)) {
+        (chain_forced || (P.n_layers() >= 9 && longest >= 9))) {
         const double other = layers_cost(P, 1);
         Plan C;
         bool uns = false;

@@ -237,10 +237,11 @@ AddPasses make_add_passes(const Plan &P, int cover);
 // The independent component of every convolution job; returns their number.
 int32_t job_components(const Plan &P, std::vector<int32_t> &comp);
 // What the blocked kernels need of a plan: 32-bit byte offsets into its
-// workspace, and that `over` coefficients before and past every job's second
-// operand lie inside it.
+// workspace, and that `before` and `past` coefficients before and past every
+// job's second operand lie inside it.
+int block_terms_of(int w, int d);
 bool small_workspace(const Plan &P);
-bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs, int over);
+bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs, int before, int past);
 // The rules every plan meets (Section 5: the jobs of one layer are
 // independent): a job reads only slots written at an earlier stage (inputs,
 // an earlier layer or level); no two jobs of a stage write one slot, and no
