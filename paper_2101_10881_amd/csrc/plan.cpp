@@ -364,11 +364,11 @@ static long mac_instr(const Plan &P) {
 // each, for every wavefront (measured: two or more wavefronts issue one
 // instruction every 4.4 to 5 cycles between them, a lone one every 7, 6 and 5.5
 // cycles at R = 1, 2 and 4), and a lone one also waits for its operands.
-static double block_iteration(const Plan &P, int R, int U, double k) {
+static double block_iteration(const Plan &P, int R, int U, double k, double lone1 = 1.5) {
     const int w = P.w;
     const double instr = (double)R * U * mac_instr(P) + 2.0 * w * R + (R == 1 ? 2.0 * w * (U - 1) : 1.0 * w * R * (R - 1)) +
                          1.0 * U * w + 40;
-    const double lone = R == 1 ? 1.5 : R == 2 ? 1.4 : 1.25, share = R > 1 ? 1.0 : k < 3 ? 1.08 : 1.04;
+    const double lone = R == 1 ? lone1 : R == 2 ? 1.4 : 1.25, share = R > 1 ? 1.0 : k < 3 ? 1.08 : 1.04;
     return std::max(4.4 * instr * share * k, 4.4 * instr * lone + 350);
 }
 
@@ -397,9 +397,10 @@ bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs
 
 // Whether the staged launches of width w and degree d run blocks.  Against the
 // coefficient-by-coefficient kernel (p1, d = 8 / 31 / 63 / 95 / 152, wall time):
-// two doubles per coefficient 1.27 / 0.99 / 1.33 / 1.18 / 1.31 times as fast,
-// (one: 0.86 to 0.93 at d = 31 to 95 on p1's layers of up to 5460 jobs, 1.06 to
-// 1.16 on p3's of 16256, 1.1 from d = 128 on),
+// two doubles per coefficient 1.27 / 0.99 / 1.33 / 1.18 / 1.31 times as fast
+// (one: 0.86 to 0.93 at d = 31 to 95 on p1's layers of up to 5460 jobs, 1.0 at
+// d = 128 to 191, 0.54 to 0.8 there on layers of 36 to 1100; on p3's of 16256
+// 1.22 and 1.34 at d = 32 and 64),
 // three 1.51 / 1.10 / 1.18 / 1.13 / 1.10, four 1.39 / 1.04 / 1.09 / 1.06 / 1.05,
 // five 1.30 / 1.02 / 1.04 / 1.02 / 0.98, eight 1.09 / 1.00 / 0.99 / 0.98 / 0.99:
 // what blocks save is the ~60 instructions a step spends around its
@@ -410,7 +411,7 @@ static bool blocks_pay(const Plan &P) {
     if (P.w > 1) return P.w <= 4 || (P.w == 5 && P.d <= 127) || P.d <= 16;
     long most = 0;
     for (int L = 1; L <= P.n_layers(); ++L) most = std::max(most, (long)(P.conv_off[L] - P.conv_off[L - 1]));
-    return P.d >= 128 || most > 6144;
+    return most > 6144;
 }
 
 // Terms an iteration of the blocked per-layer and fused launches takes: four
@@ -968,7 +969,18 @@ static double chain_cost(const Plan &P, size_t chains, int R, int U, int W, int 
     const long per_cu = std::min(fit, ((long)chains + cus - 1) / cus);
     const double rounds = std::ceil(chains / (double)(cus * per_cu));
     const double k = std::max(1.0, per_cu * W / 4.0);  // wavefronts per SIMD
-    return rounds * steps * (block_iteration(P, R, U, k) + (W > 1 ? (60.0 + 30.0 * W) / S : 0));
+    // (fewer than four, long products: 226 chains of 23 at eight doubles, d = 15,
+    // took 227 us on two wavefronts and 207 on four where the terms above tie)
+    const double few = W < 4 && P.w >= 8 ? 1.1 : 1.0;
+    // With a chain per CU at most and from five doubles on, whose products hold
+    // independent sums, a lone wavefront issues every 5 cycles or so: four
+    // wavefronts, not eight, for chains of 23 to 64 (d = 49: 10 doubles 907
+    // against 1072 us, 8 538 against 606, 5 209 against 227).  With more chains
+    // the estimate of the rounds, made for equal chains, is the larger error and
+    // keeps the factor of the narrow ones (211 monomials of 1 to 12 variables,
+    // 8 doubles, d = 70: 693 us; with this factor 1146).
+    const double lone = chains > (size_t)cus || P.w < 5 ? 1.5 : P.w == 5 ? 1.2 : 1.12;
+    return few * rounds * steps * (block_iteration(P, R, U, k, lone) + (W > 1 ? (60.0 + 30.0 * W) / S : 0));
 }
 
 // The chain launch for a plan without in-place jobs: the cheapest estimate
@@ -1017,7 +1029,7 @@ static bool choose_chain_launch(Plan &P, bool forced, double other) {
                 // needs no spills; one or two only for many chains
                 if ((W > 8 && P.w * u1 > 10) || (W == 16 && P.w > 8)) continue;
                 if (W < 4 && (R == 0 || chains.size() < 64)) continue;
-                for (int S : {1, 2}) {
+                for (int S : {1, 2, 4}) {
                     if (W == 1 && S > 1) continue;
                     // (not worth a schedule if its fewest iterations cost more than the best)
                     const int items = P.d / r1, tail = R == 1 ? P.d / u1 + 1 : items + 1;

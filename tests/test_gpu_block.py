@@ -40,9 +40,9 @@ def test_layer_and_fused_launches(oracle_lib, m, d, cx, fused):
     _check(oracle_lib, w, fused_layers=fused)
 
 
-# one double takes four coefficients per lane from d = 128 on, or in layers of
-# more than 6144 jobs
-@pytest.mark.parametrize("d,n", [(128, 12), (131, 12), (3, 70), (10, 70)])
+# one double runs blocks, of four coefficients where that is cheapest, in layers
+# of more than 6144 jobs
+@pytest.mark.parametrize("d,n", [(128, 12), (131, 80), (3, 80), (10, 80), (67, 80)])
 def test_four_coefficients_per_lane(oracle_lib, d, n):
     _check(oracle_lib, W.make("quad", 1, d, n, W.all_subsets(n, 2 if n > 20 else 3), seed=d), fused_layers=False)
 
