@@ -8,12 +8,14 @@
 namespace mdpe {
 
 // WPB wavefronts per workgroup (1 or 4), each with its own group of J jobs in
-// its own LDS region; Q wavefronts share each group (Q > 1: J = 1).
-template <int M, bool CORR, bool CX, int R, int U, int WPB>
+// its own LDS region; Q wavefronts share each group (Q > 1: J = 1).  LONE: for
+// launches of at most one wavefront per SIMD (one_per_simd).
+template <int M, bool CORR, bool CX, int R, int U, int WPB, bool LONE = false>
 __global__ __launch_bounds__(64 * WPB) void conv_block_kernel(double *__restrict__ A, const int4 *__restrict__ jobs,
                                                               int njobs, int d, int J, const int *__restrict__ chains,
                                                               int stride, int its, int group_bytes, int Q) {
     extern __shared__ double lds[];
+    if constexpr (LONE) one_per_simd();
     const int wave = WPB == 1 ? 0 : (int)(threadIdx.x >> 6);
     const int wv = blockIdx.x * WPB + wave;
     const int g = Q == 1 ? wv : wv / Q;
@@ -81,6 +83,9 @@ int launch_r(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipStream
         hipError_t e = hipFuncSetAttribute((const void *)conv_block_kernel<M, CORR, CX, R, U, 1>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLdsBytes);
         if (e == hipSuccess)
+            e = hipFuncSetAttribute((const void *)conv_block_kernel<M, CORR, CX, R, U, 1, true>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLdsBytes);
+        if (e == hipSuccess)
             e = hipFuncSetAttribute((const void *)conv_block_kernel<M, CORR, CX, R, U, 4>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLdsBytes);
         if (e != hipSuccess) return fail(MDPE_EDEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(e));
@@ -92,6 +97,9 @@ int launch_r(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipStream
     if (waves <= 3L * simds && waves > simds && 4 * bytes <= (size_t)kMaxLdsBytes)
         hipLaunchKernelGGL((conv_block_kernel<M, CORR, CX, R, U, 4>), dim3((unsigned)((waves + 3) / 4)), dim3(256),
                            4 * bytes, st, A, jobs, nj, P.d, J, pl->d_blocks, ls.stride, ls.steps, (int)bytes, Q);
+    else if (waves <= simds && waves > simds / 4)
+        hipLaunchKernelGGL((conv_block_kernel<M, CORR, CX, R, U, 1, true>), dim3((unsigned)waves), dim3(64), bytes, st, A,
+                           jobs, nj, P.d, J, pl->d_blocks, ls.stride, ls.steps, (int)bytes, Q);
     else
         hipLaunchKernelGGL((conv_block_kernel<M, CORR, CX, R, U, 1>), dim3((unsigned)waves), dim3(64), bytes, st, A, jobs,
                            nj, P.d, J, pl->d_blocks, ls.stride, ls.steps, (int)bytes, Q);

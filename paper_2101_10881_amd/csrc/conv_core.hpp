@@ -303,12 +303,14 @@ __device__ __forceinline__ void conv_group(double *__restrict__ A, const int4 *_
 // part w % Q.
 // MQ = false: one wavefront per group (Q = 1), the mapping without a division
 // (a separate instantiation so that the common case's code is unchanged).
-template <int M, bool CORR, bool CX = false, int WPB = 1, bool XS = false, bool MQ = XS>
+// LONE: for launches of at most one wavefront per SIMD (one_per_simd).
+template <int M, bool CORR, bool CX = false, int WPB = 1, bool XS = false, bool MQ = XS, bool LONE = false>
 __global__ __launch_bounds__(64 * WPB) void conv_layer_kernel(double *__restrict__ A, const int4 *__restrict__ jobs,
                                                               int njobs, int d, int J, const int *__restrict__ chains,
                                                               int stride, int steps, int group_bytes, int Q,
                                                               int simple) {
     extern __shared__ double lds[];
+    if constexpr (LONE) one_per_simd();
     const int wave = WPB == 1 ? 0 : (int)(threadIdx.x >> 6);
     const int wv = blockIdx.x * WPB + wave;
     const int g = MQ ? wv / Q : wv;

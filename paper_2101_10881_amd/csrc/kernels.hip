@@ -350,6 +350,8 @@ int launch_layer(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipSt
     if (!attr_set[dv].load()) {
         HIP_TRY(hipFuncSetAttribute((const void *)mdpe::conv_layer_kernel<M, CORR, CX, 1, false>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)mdpe::kMaxLdsBytes));
+        HIP_TRY(hipFuncSetAttribute((const void *)mdpe::conv_layer_kernel<M, CORR, CX, 1, false, false, true>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)mdpe::kMaxLdsBytes));
         HIP_TRY(hipFuncSetAttribute((const void *)mdpe::conv_layer_kernel<M, CORR, CX, 4, false>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)mdpe::kMaxLdsBytes));
         HIP_TRY(hipFuncSetAttribute((const void *)mdpe::conv_layer_kernel<M, CORR, CX, 1, false, true>,
@@ -401,6 +403,10 @@ int launch_layer(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipSt
             hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 4, false>), dim3((unsigned)blocks), dim3(256),
                                4 * group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains, P.lanes.stride, P.lanes.steps,
                                (int)group_bytes, 1, P.simple ? 1 : 0);
+        else if (waves <= simds && waves > simds / 4)  // (fewer: room for two streams' launches)
+            hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 1, false, false, true>), dim3((unsigned)blocks),
+                               dim3(64), group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains, P.lanes.stride,
+                               P.lanes.steps, (int)group_bytes, 1, P.simple ? 1 : 0);
         else
             hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 1, false>), dim3((unsigned)blocks), dim3(64),
                                group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains, P.lanes.stride, P.lanes.steps,
