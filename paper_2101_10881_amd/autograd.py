@@ -30,6 +30,8 @@ class PolyEvalFunction(torch.autograd.Function):
         ctx.poly = poly
         ctx.ws = ws
         ctx.mark_non_differentiable(grad)
+        # no zeros made for the gradient output's unused adjoint
+        ctx.set_materialize_grads(False)
         ctx.save_for_backward(grad)
         return value, grad
 

@@ -9,23 +9,30 @@
 //
 // Kernels
 //   stage_kernel         user coeff / z -> input slots of A (+ n_k = 1 copies)
-//   conv_layer_kernel    one wavefront per group of J jobs of a layer (four per
-//                        workgroup when a launch has one to three wavefronts
-//                        per SIMD; or Q wavefronts per job, J = 1, for layers
-//                        of few long jobs) stages the jobs' first operands in
-//                        LDS (both operands for coefficients of at most two
-//                        doubles; none when operands are streamed) and
-//                        computes their J*(d+1) output coefficients;
-//                        each coefficient is one lane's sequential chain
+//   conv_block_kernel    (block.hip) the convolutions of a layer, several terms
+//                        of a coefficient per iteration: two to five doubles per
+//                        coefficient, short series beyond, large layers of one
+//   conv_layer_kernel    the same one term at a time, for the other widths and
+//                        workspaces of 4 GiB and more: one wavefront per group of
+//                        J jobs of a layer (four per workgroup when a launch has
+//                        one to three wavefronts per SIMD; or Q wavefronts per
+//                        job, J = 1, for layers of few long jobs) stages the jobs'
+//                        first operands in LDS (both operands for coefficients of
+//                        at most two doubles; none when operands are streamed) and
+//                        computes their J*(d+1) output coefficients; each
+//                        coefficient is one lane's sequential chain
 //                        z_k = x_0 y_k, z_k += x_i y_{k-i} (i = 1..k), spread
 //                        over the lanes by a host-made schedule or dealt to the
 //                        lanes in turn (Section 2, eq. (1); Section 5, the
 //                        convolution kernel); complex series and the
-//                        correlations of the reverse pass run on it too
+//                        correlations of the reverse pass run on both
 //   scale_kernel         A[dst] := e * A[src] for general exponents (Section 3)
-//   add_level_kernel     one thread per coefficient of every pair of a level:
-//                        A[t2] := A[t2] + A[t1] (Section 5, the addition kernel)
-//   gather_kernel        output slots -> user value / gradient (zeros if absent)
+//   add_tree_kernel      (addtree.hip) the pairwise sums of every output in one or
+//                        two passes, the last into the user's value / gradient
+//                        (Section 5, the addition kernel; zeros if absent)
+//   eval_single_kernel   all of it in one workgroup, for the smallest plans
+//   reverse_stage_kernel, reverse_gather_kernel
+//                        the reverse pass's operands and results
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -78,16 +85,24 @@ __global__ __launch_bounds__(256) void scale_kernel(double *__restrict__ A, cons
     scale_item<M, CX>(A, jobs[q], (int)(idx - q * d1), d);
 }
 
+// One thread per double, in the workspace's order: stores are coalesced and loads
+// run along the planes of the planar inputs.  (A thread per coefficient with a
+// loop over its limbs: 8128 products of two at three doubles, d = 95, 10.2 us.)
 __global__ __launch_bounds__(256) void stage_kernel(double *__restrict__ A, const double *__restrict__ coeff,
                                                     const double *__restrict__ z, const int2 *__restrict__ entries,
                                                     long total, int N, int n, int d, int m) {
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
-    const int d1 = d + 1;
-    const long e = idx / d1;
-    const int c = (int)(idx - e * d1);
-    stage_item(A, coeff, z, entries[e], c, N, n, d, m);
+    const int d1 = d + 1, S = d1 * m;
+    for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256) {
+        const long e = idx / S;
+        const int r = (int)(idx - e * S), c = r / m, l = r - c * m;
+        const int2 en = entries[e];
+        A[(long)en.x * S + r] = en.y <= N ? coeff[((long)l * (N + 1) + en.y) * d1 + c]
+                                          : z[((long)l * n + (en.y - N - 1)) * d1 + c];
+    }
 }
+
+// Workgroups of a kernel of one thread per item that strides over the rest.
+static unsigned copy_blocks(long items) { return (unsigned)std::min((items + 255) / 256, 1L << 20); }
 
 // The whole evaluation in one launch of one workgroup, for plans so small
 // that the boundaries between dependent launches (~4.5 us each) would
@@ -171,31 +186,42 @@ __global__ __launch_bounds__(1024) void eval_single_kernel(SingleArgs a) {
     for (long q = tid; q < a.ws_doubles; q += nt) a.A[q] = A[q];
 }
 
-// planar [m][count][d+1] series src[e] -> slot dst[e] (skipped when -1), for e < count
-__global__ __launch_bounds__(256) void planar_to_slots_kernel(double *__restrict__ A, const double *__restrict__ src,
-                                                              int count, const int *__restrict__ dst, long total,
-                                                              int d, int m) {
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
-    const int d1 = d + 1;
-    const int e = (int)(idx / d1);
-    const int c = (int)(idx - (long)e * d1);
-    if (dst[e] < 0) return;
-    double *to = A + (long)dst[e] * d1 * m + (long)c * m;
-    for (int l = 0; l < m; ++l) to[l] = src[((long)l * count + e) * d1 + c];
+// The reverse pass's operands into the workspace: ybar into slot ybar_slot,
+// gradient series i (planar [m][n][d+1]) into slot grad_slots[i] (skipped when
+// -1).  One launch and one double per thread, as in stage_kernel: two launches
+// with a loop over the limbs each cost 4 to 6 us, all of it the kernel boundary
+// and the loop's latency.
+__global__ __launch_bounds__(256) void reverse_stage_kernel(double *__restrict__ A, const double *__restrict__ ybar,
+                                                            const double *__restrict__ grad, const int *__restrict__ ybar_slot,
+                                                            const int *__restrict__ grad_slots, int n, int d, int m) {
+    const int d1 = d + 1, S = d1 * m;
+    const long total = (long)(1 + n) * S;
+    for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256) {
+        const long e = idx / S - 1;
+        const int r = (int)(idx - (e + 1) * S), c = r / m, l = r - c * m;
+        const int slot = e < 0 ? *ybar_slot : grad_slots[e];
+        if (slot >= 0) A[(long)slot * S + r] = e < 0 ? ybar[(long)l * d1 + c] : grad[((long)l * n + e) * d1 + c];
+    }
 }
 
-// slot slots[e] (or zeros when -1) -> planar [m][count][d+1] series e of dst
-__global__ __launch_bounds__(256) void slots_to_planar_kernel(const double *__restrict__ A, double *__restrict__ dst,
-                                                              int count, const int *__restrict__ slots, int d, int m) {
-    const long idx = (long)blockIdx.x * 256 + threadIdx.x;
-    const int d1 = d + 1;
-    if (idx >= (long)count * d1) return;
-    const int e = (int)(idx / d1);
-    const int c = (int)(idx - (long)e * d1);
-    const int slot = slots[e];
-    for (int l = 0; l < m; ++l)
-        dst[((long)l * count + e) * d1 + c] = slot >= 0 ? A[(long)slot * d1 * m + (long)c * m + l] : 0.0;
+// The reverse pass's results out of it: slots cbar (N1 = N + 1 series) into
+// coeff_bar and zbar (n) into z_bar, zeros for -1.
+__global__ __launch_bounds__(256) void reverse_gather_kernel(const double *__restrict__ A, double *__restrict__ coeff_bar,
+                                                             double *__restrict__ z_bar, const int *__restrict__ cbar,
+                                                             const int *__restrict__ zbar, int N1, int n, int d, int m) {
+    const int d1 = d + 1, S = d1 * m;
+    const long total = ((long)N1 + n) * S;
+    for (long idx = (long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long)gridDim.x * 256) {
+        const long e = idx / S;
+        const int r = (int)(idx - e * S), c = r / m, l = r - c * m;
+        const bool z = e >= N1;
+        const int slot = z ? zbar[e - N1] : cbar[e];
+        const double v = slot >= 0 ? A[(long)slot * S + r] : 0.0;
+        if (z)
+            z_bar[((long)l * n + (e - N1)) * d1 + c] = v;
+        else
+            coeff_bar[((long)l * N1 + e) * d1 + c] = v;
+    }
 }
 
 // op 0 / 1: md_add / md_mul on planar [M][count]; CX: cmd_add / cmd_mul on [2M][count]
@@ -371,8 +397,8 @@ int launch_layer(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipSt
         const long waves = (long)groups * Q;
         if (waves > 0x7fffffffL) return fail(MDPE_EUNSUPPORTED, "too many wavefronts in one layer");
         hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 1, true>), dim3((unsigned)waves), dim3(64),
-                           group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains, P.lanes.stride, P.lanes.steps,
-                           (int)group_bytes, Q, 0);
+                           group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains,
+                           P.lanes.stride, P.lanes.steps, (int)group_bytes, Q, 0);
     } else {
         const size_t group_bytes =
             (conv_lds_bytes(P.d, mdpe::lds_doubles_per_coef(mdpe::kCoef<M, CX>), J) + 15) / 16 * 16;
@@ -393,24 +419,25 @@ int launch_layer(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipSt
         if (dealt4) {
             if constexpr (mdpe::kCoef<M, CX> <= 2)
                 hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 4, false, true>),
-                                   dim3((unsigned)((waves + 3) / 4)), dim3(256), 4 * group_bytes, st, A, jobs, nj, P.d,
-                                   J, pl->d_chains, P.lanes.stride, P.lanes.steps, (int)group_bytes, Q, 1);
+                                   dim3((unsigned)((waves + 3) / 4)), dim3(256),
+                                   4 * group_bytes, st, A, jobs, nj, P.d, J,
+                                   pl->d_chains, P.lanes.stride, P.lanes.steps, (int)group_bytes, Q, 1);
         } else if (Q > 1)
             hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 1, false, true>), dim3((unsigned)waves), dim3(64),
-                               group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains, P.lanes.stride, P.lanes.steps,
-                               (int)group_bytes, Q, P.simple ? 1 : 0);
+                               group_bytes, st, A, jobs, nj, P.d, J,
+                               pl->d_chains, P.lanes.stride, P.lanes.steps, (int)group_bytes, Q, P.simple ? 1 : 0);
         else if (wpb == 4)
             hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 4, false>), dim3((unsigned)blocks), dim3(256),
-                               4 * group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains, P.lanes.stride, P.lanes.steps,
-                               (int)group_bytes, 1, P.simple ? 1 : 0);
+                               4 * group_bytes, st, A, jobs, nj, P.d, J,
+                               pl->d_chains, P.lanes.stride, P.lanes.steps, (int)group_bytes, 1, P.simple ? 1 : 0);
         else if (waves <= simds && waves > simds / 4)  // (fewer: room for two streams' launches)
             hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 1, false, false, true>), dim3((unsigned)blocks),
                                dim3(64), group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains, P.lanes.stride,
                                P.lanes.steps, (int)group_bytes, 1, P.simple ? 1 : 0);
         else
             hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 1, false>), dim3((unsigned)blocks), dim3(64),
-                               group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains, P.lanes.stride, P.lanes.steps,
-                               (int)group_bytes, 1, P.simple ? 1 : 0);
+                               group_bytes, st, A, jobs, nj, P.d, J,
+                               pl->d_chains, P.lanes.stride, P.lanes.steps, (int)group_bytes, 1, P.simple ? 1 : 0);
     }
     LAUNCH_CHECK("conv_layer_kernel");
     return record(prof, 1, st, false);
@@ -435,8 +462,8 @@ int launch_fused(const mdpe_plan *pl, double *A, hipStream_t st, mdpe_profiler *
     int rc = record(prof, 1, st, true);
     if (rc) return rc;
     hipLaunchKernelGGL((mdpe::conv_fused_kernel<M, CX>), dim3((unsigned)P.fused_components), dim3(64 * waves),
-                       waves * group_bytes, st, A, pl->d_fconv, pl->d_foff, P.n_layers(), P.d, J, pl->d_fchains,
-                       P.fused_lanes.stride, P.fused_lanes.steps, (int)group_bytes, P.fused_simple ? 1 : 0);
+                       waves * group_bytes, st, A, pl->d_fconv,
+                       pl->d_foff, P.n_layers(), P.d, J, pl->d_fchains, P.fused_lanes.stride, P.fused_lanes.steps, (int)group_bytes, P.fused_simple ? 1 : 0);
     LAUNCH_CHECK("conv_fused_kernel");
     return record(prof, 1, st, false);
 }
@@ -617,7 +644,6 @@ int eval_impl(const mdpe_plan *pl, const double *coeff, const double *z, double 
     if (!g.ok) return fail(MDPE_EDEVICE, "cannot select the plan's device");
     hipStream_t st = (hipStream_t)stream;
     double *A = (double *)workspace;
-    const int d1 = P.d + 1;
     int rc;
     if (P.single) {
         switch (P.m) {
@@ -632,9 +658,9 @@ int eval_impl(const mdpe_plan *pl, const double *coeff, const double *z, double 
         }
     }
     {
-        const long total = (long)P.stage.size() * d1;
+        const long total = (long)P.stage.size() * (P.d + 1) * P.w;
         if ((rc = record(prof, 0, st, true))) return rc;
-        hipLaunchKernelGGL(mdpe::stage_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, A, coeff, z,
+        hipLaunchKernelGGL(mdpe::stage_kernel, dim3(mdpe::copy_blocks(total)), dim3(256), 0, st, A, coeff, z,
                            pl->d_stage, total, P.N, P.n, P.d, P.w);
         LAUNCH_CHECK("stage_kernel");
         if ((rc = record(prof, 0, st, false))) return rc;
@@ -674,19 +700,12 @@ int adjoint_impl(const mdpe_plan *pl, const double *ybar, void *workspace, const
     if (!g.ok) return fail(MDPE_EDEVICE, "cannot select the plan's device");
     hipStream_t st = (hipStream_t)stream;
     double *A = (double *)workspace;
-    const int d1 = P.d + 1;
     int rc;
     if ((rc = record(prof, 0, st, true))) return rc;
-    hipLaunchKernelGGL(mdpe::planar_to_slots_kernel, dim3((unsigned)((d1 + 255) / 256)), dim3(256), 0, st, A, ybar, 1,
-                       pl->d_ybar, (long)d1, P.d, P.m);
-    LAUNCH_CHECK("planar_to_slots_kernel");
-    {
-        // the caller's gradient g_i into the slots the correlations read
-        const long tg = (long)P.n * d1;
-        hipLaunchKernelGGL(mdpe::planar_to_slots_kernel, dim3((unsigned)((tg + 255) / 256)), dim3(256), 0, st, A, grad,
-                           P.n, pl->d_out + 1, tg, P.d, P.m);
-        LAUNCH_CHECK("planar_to_slots_kernel");
-    }
+    const long S = (long)(P.d + 1) * P.m;
+    hipLaunchKernelGGL(mdpe::reverse_stage_kernel, dim3(mdpe::copy_blocks((1 + P.n) * S)), dim3(256), 0, st, A,
+                       ybar, grad, pl->d_ybar, pl->d_out + 1, P.n, P.d, P.m);
+    LAUNCH_CHECK("reverse_stage_kernel");
     if ((rc = record(prof, 0, st, false))) return rc;
     const int nj = (int)P.corr.size();
     if (P.block_r > 0) {
@@ -706,15 +725,9 @@ int adjoint_impl(const mdpe_plan *pl, const double *ybar, void *workspace, const
     }
     if (rc) return rc;
     if ((rc = record(prof, 3, st, true))) return rc;
-    {
-        const long tc = (long)(P.N + 1) * d1, tz = (long)P.n * d1;
-        hipLaunchKernelGGL(mdpe::slots_to_planar_kernel, dim3((unsigned)((tc + 255) / 256)), dim3(256), 0, st, A,
-                           coeff_bar, P.N + 1, pl->d_cbar, P.d, P.m);
-        LAUNCH_CHECK("slots_to_planar_kernel");
-        hipLaunchKernelGGL(mdpe::slots_to_planar_kernel, dim3((unsigned)((tz + 255) / 256)), dim3(256), 0, st, A,
-                           z_bar, P.n, pl->d_zbar, P.d, P.m);
-        LAUNCH_CHECK("slots_to_planar_kernel");
-    }
+    hipLaunchKernelGGL(mdpe::reverse_gather_kernel, dim3(mdpe::copy_blocks(((long)P.N + 1 + P.n) * S)), dim3(256), 0, st, A,
+                       coeff_bar, z_bar, pl->d_cbar, pl->d_zbar, P.N + 1, P.n, P.d, P.m);
+    LAUNCH_CHECK("reverse_gather_kernel");
     return record(prof, 3, st, false);
 }
 
