@@ -752,7 +752,7 @@ void launch_elementwise(int op, long count, const double *x, const double *y, do
 // writes the inputs, and every convolution and addition writes its output
 // slot before any job reads it.
 namespace {
-constexpr int64_t kScratchBytes = 64ll << 20;
+using mdpe::kScratchBytes;
 static __device__ __align__(256) double scratch[kScratchBytes / sizeof(double)];
 
 // The array's device address on `device` (each device holds its own copy).

@@ -13,6 +13,7 @@
 namespace mdpe {
 
 constexpr int kLanes = 64;             // one wavefront per convolution workgroup
+constexpr int64_t kScratchBytes = 64ll << 20;  // workspace of the allocation-free entry
 constexpr int kMaxLdsBytes = 163840;   // LDS one gfx950 workgroup may allocate
 constexpr int kLdsBudget = 65536;      // LDS a workgroup aims to stay under (>= 2 per CU)
 constexpr int kMaxExponent = 64;
