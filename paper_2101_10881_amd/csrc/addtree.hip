@@ -23,7 +23,7 @@ __host__ __device__ constexpr int add_run(int w) { return w <= 8 ? 8 : 4; }
 // the tree's own pairs (later element + earlier one, an odd one carried), so
 // every sum is that of the level-by-level additions.  Bound by the latency of
 // a pass at these sizes: one launch per level (each ~4.7 us, bound by its
-// boundary) took 35-77 us for 8 to 13 levels, a pass takes 5 to 10 us.  Each
+// boundary) took 35-77 us for 8 to 13 levels, a pass takes 4 to 13 us.  Each
 // leaf is read once and each part written once, where a launch per level
 // reads two series and writes one per addition.
 template <int M, bool CX>

@@ -7,13 +7,23 @@
 // its signalling.  The tasks form one queue, ordered by pipeline depth, so a
 // task only ever depends on earlier tasks.
 //
+// A task costs 32 ns (convolution) to 100 ns (addition) of the launch in fences
+// and the claim, whatever it does (measured with more and smaller tasks).  So, at
+// two to five doubles per coefficient, convolutions run by blocks (conv_block.hpp)
+// and, where a queue holds at least kSetComponents independent components, a task
+// is a set of whole components, every layer of them, and no wait lies between the
+// layers; additions run by passes over whole output lists, the last into the
+// user's buffers, instead of a stage per level and a gather.  128 mixed instances
+// (2 and 4 doubles, d = 8 to 128): 12.3 -> 7.9 ms, 512: 32.8 -> 27.
+//
 // Instances are spread over one queue per XCD (the MI355X has 8 XCDs, each
 // with its own L2), balancing estimated cost; all tasks of an instance sit in
 // one queue, except for an instance costing more than an eighth of the batch
 // (a batch of one), whose tasks are dealt over all queues in turn.  Each
-// queue is ordered by pipeline depth.  One persistent kernel of one-wavefront workgroups (as many as
-// are resident, rounded down to equal numbers per SIMD) reads the XCD it runs on from the XCC_ID hardware register
-// and claims tasks of that XCD's queue with an atomic counter, so an
+// queue is ordered by pipeline depth.  One persistent kernel of one-wavefront
+// workgroups (equal numbers per SIMD: two, or three for many tasks, by blocks,
+// else as many as are resident) reads the XCD it runs on from the XCC_ID
+// hardware register and claims tasks of that XCD's queue with an atomic counter, so an
 // instance's data stays near one L2.  A task of stage s of instance p waits
 // until p's completion counter reaches the number of p's tasks in stages
 // before s (agent-scope acquire), runs, then increments the counter

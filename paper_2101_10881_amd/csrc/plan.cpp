@@ -563,13 +563,16 @@ static bool balance_layers(Plan &P, long per_round) {
     for (long j = nj - 1; j >= 0; --j)
         for (int q = sbeg[j]; q < sbeg[j + 1]; ++q) latest[j] = std::min(latest[j], latest[succ[q]] - 1);
     std::vector<int> layer(nj, 0), ready, next;
+    std::vector<int64_t> keys;
     for (long j = 0; j < nj; ++j)
         if (npred[j] == 0) ready.push_back((int)j);
     long placed = 0;
     for (int L = 1; L <= D; ++L) {
-        std::sort(ready.begin(), ready.end(), [&](int a, int b) {
-            return latest[a] != latest[b] ? latest[a] < latest[b] : a < b;
-        });
+        // (latest, job) packed in one key: cheaper to sort than by look-ups
+        keys.resize(ready.size());
+        for (size_t q = 0; q < ready.size(); ++q) keys[q] = (int64_t)latest[ready[q]] << 32 | (int64_t)ready[q];
+        std::sort(keys.begin(), keys.end());
+        for (size_t q = 0; q < ready.size(); ++q) ready[q] = (int)(keys[q] & 0x7fffffff);
         const long nr = (long)ready.size();
         long mand = 0;
         while (mand < nr && latest[ready[mand]] <= L) ++mand;
