@@ -65,7 +65,8 @@ def progress(msg):
 
 def kernel_source_digest():
     h = hashlib.sha256()
-    for f in ("md.hpp", "conv_core.hpp", "kernels.hip", "plan.cpp", "plan.hpp"):
+    for f in ("md.hpp", "conv_core.hpp", "conv_block.hpp", "kernels.hip", "block.hip", "chain.hip", "addtree.hip", "plan.cpp",
+              "plan.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2101_10881_amd", "csrc", f), "rb").read())
     return h.hexdigest()
 

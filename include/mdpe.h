@@ -200,8 +200,8 @@ typedef struct {
     int32_t chain_layers;   /* MDPE_CHAIN_LAUNCH: layers 1..chain_layers run in the chain launch
                                (layer L: the L-th product of every chain); 0 without it */
     int32_t chain_count;    /* MDPE_CHAIN_LAUNCH: chains, one workgroup each */
-    int32_t chain_waves;    /* MDPE_CHAIN_LAUNCH: wavefronts per chain workgroup (4, 8, 12 or 16) */
-    int32_t chain_window;   /* MDPE_CHAIN_LAUNCH: steps between workgroup barriers */
+    int32_t chain_waves;    /* MDPE_CHAIN_LAUNCH: wavefronts per chain workgroup (1, 2, 4, 8, 12 or 16) */
+    int32_t chain_window;   /* MDPE_CHAIN_LAUNCH: iterations between workgroup barriers */
     int32_t chain_ring;     /* MDPE_CHAIN_LAUNCH: LDS slots of first operands per chain */
     int32_t single_launch;  /* 1 if the whole evaluation runs in one workgroup (MDPE_SINGLE_LAUNCH) */
     int32_t single_waves;   /* MDPE_SINGLE_LAUNCH: wavefronts of that workgroup */
@@ -418,8 +418,9 @@ int md_elementwise(int op, int m, int64_t count, const double *x, const double *
 /* ------------------------------------------------------- batched plans --
  * Many polynomials in one persistent launch.  The batch references its plans
  * (which must outlive it); each instance keeps its own buffers.  All stages
- * of all instances (staging, convolution layers, addition levels, gather)
- * become tasks; each instance goes whole to one of 8 queues, one per XCD,
+ * of all instances (staging, convolutions, additions, gather) become tasks
+ * (at two to five doubles whole components, every layer of them, and passes
+ * over whole output lists); each instance goes whole to one of 8 queues, one per XCD,
  * balanced by estimated cost, so that producers and consumers of an instance
  * share one L2 -- except an instance whose estimated cost exceeds an eighth
  * of the batch (a batch of one), whose tasks, one group of jobs each, are
