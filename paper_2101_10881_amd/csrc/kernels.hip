@@ -88,8 +88,8 @@ __global__ __launch_bounds__(256) void scale_kernel(double *__restrict__ A, cons
 // Bound by the copy (p1 at ten doubles, d = 152: 180 MB in 12.5 us, from the
 // caches) or, when small, by the launch.  One thread per double, in the
 // workspace's order: stores are coalesced and loads run along the planes of the
-// planar inputs.  A thread per coefficient with a loop over its limbs took 5.2 and
-// 5.6 us where this takes 4.7 and 4.9 (one double d = 152, five d = 37), and 10.2
+// planar inputs.  A thread per coefficient with a loop over its limbs took 37.6 us
+// there, 5.2 and 5.6 us where this takes 4.7 and 4.9 (one double d = 152, five d = 37), and 10.2
 // against 11.1 at 8128 products of two, three doubles, d = 95.
 __global__ __launch_bounds__(256) void stage_kernel(double *__restrict__ A, const double *__restrict__ coeff,
                                                     const double *__restrict__ z, const int2 *__restrict__ entries,
