@@ -37,9 +37,9 @@ class PolyEvalFunction(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, ybar, _grad_bar):
-        if ybar is None:
-            return None, None, None
         (grad,) = ctx.saved_tensors
+        if ybar is None:  # no adjoint reached the value: a zero one
+            ybar = grad.new_zeros((ctx.poly.m, ctx.poly.d + 1))
         cbar, zbar = ctx.poly.adjoint(ybar.contiguous(), grad, workspace=ctx.ws)
         return cbar, zbar, None
 
