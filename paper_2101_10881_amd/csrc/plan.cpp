@@ -1188,11 +1188,11 @@ static std::string build_plan_launches(int n, int N, int d, int m, const int32_t
         bool uns = false;
         std::string e2 = build_plan_mode(n, N, d, m, nvars, vars, exps, flags, false, true, C, &uns);
         if (e2.empty() && choose_chain_launch(C, chain_forced, other)) {
-            // (a plan of short chains that the allocation-free entry takes without
-            // the chain launch's fresh slots is not made too large for it)
+            // (a plan that the allocation-free entry takes without the chain launch's
+            // fresh slots is not made too large for it)
             auto bytes = [](const Plan &Q) { return Q.n_series * (int64_t)(Q.d + 1) * Q.w * (int64_t)sizeof(double); };
             const bool outgrows = bytes(P) <= kScratchBytes && bytes(C) > kScratchBytes;
-            if (chain_forced || P.n_layers() >= 16 || !outgrows) {
+            if (chain_forced || !outgrows) {
                 auto h = check_hazards(C);
                 if (!h.empty()) return "internal planner error (chain launch): " + h;
                 P = std::move(C);
