@@ -89,6 +89,7 @@ constexpr int kSpinLimit = 1 << 22;
 constexpr int kQueues = 8;  // one task queue per XCD
 constexpr int kSummed = -2;
 constexpr int kSetComponents = 256;  // resident wavefronts of an XCD (32 CUs x 8)
+constexpr double kSetOverLayers = 1.4;
 
 // the XCD (XCC) this wavefront runs on
 __device__ __forceinline__ int xcd_id() { return (int)(__builtin_amdgcn_s_getreg(20 | (15 << 11)) & (kQueues - 1)); }
@@ -785,6 +786,29 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         comps[p] = mdpe::job_components(plans[p]->P, comp[p]);
         queue_comps[B->inst_queue[p]] += comps[p];
     }
+    // each instance's lane schedule, and each queue's convolution time: groups x
+    // steps x the cost of a step (a component set's below, in the same unit)
+    std::vector<int> sched_of(count);
+    std::vector<double> queue_time(mdpe::kQueues, 0.0);
+    auto step_cost = [&](const mdpe::Plan &P) { return mdpe::batch_terms(P.m) * P.m * P.m + 10.0; };
+    for (int p = 0; p < count; ++p) {
+        const mdpe::Plan &P = plans[p]->P;
+        const int J = tile_for(P.m, P.d).jobs_per_group;
+        const std::array<int, 3> key{P.d, J, B->blocks ? mdpe::batch_terms(P.m) : 0};
+        if (!sched_index.count(key)) {
+            sched_index[key] = (int)scheds.size();
+            scheds.push_back(B->blocks ? mdpe::make_block_schedule(P.d, 1, mdpe::batch_terms(P.m), J, 1)
+                                       : mdpe::make_lane_schedule(P.d, J));
+        }
+        sched_of[p] = sched_index[key];
+        double groups = 0;
+        for (int L = 1; L <= P.n_layers(); ++L) groups += (double)((P.conv_off[L] - P.conv_off[L - 1] + J - 1) / J);
+        const double t = groups * scheds[sched_of[p]].steps * step_cost(P);
+        if (B->inst_queue[p] >= 0)
+            queue_time[B->inst_queue[p]] += t;
+        else
+            for (double &x : queue_time) x += t / mdpe::kQueues;
+    }
     B->set_jobs.resize(count);
     B->set_groups.resize(count);
     std::vector<Tmp> tmp;
@@ -802,13 +826,7 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         const mdpe::Plan &P = plans[p]->P;
         const mdpe_batch_tile t = tile_for(P.m, P.d);
         const int J = t.jobs_per_group;
-        const std::array<int, 3> key{P.d, J, B->blocks ? mdpe::batch_terms(P.m) : 0};
-        if (!sched_index.count(key)) {
-            sched_index[key] = (int)scheds.size();
-            scheds.push_back(B->blocks ? mdpe::make_block_schedule(P.d, 1, mdpe::batch_terms(P.m), J, 1)
-                                       : mdpe::make_lane_schedule(P.d, J));
-        }
-        const mdpe::LaneSchedule &S = scheds[sched_index[key]];
+        const mdpe::LaneSchedule &S = scheds[sched_of[p]];
         const int terms = S.steps * (B->blocks ? mdpe::batch_terms(P.m) : 1);
         // a dealt instance finds its parallelism inside its own layers: one
         // group of jobs per task, small addition tasks
@@ -852,7 +870,7 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         // stage
         done_before += items(0, (long)P.stage.size() * d1);
         ++depth;
-        const bool by_sets = !dealt && comps[p] > 0 && queue_comps[queue] >= mdpe::kSetComponents;
+        bool by_sets = !dealt && comps[p] > 0 && queue_comps[queue] >= mdpe::kSetComponents;
         if (by_sets) {
             // 2J components per set, so that a layer's jobs fill groups of J (a
             // tile may ask for more work per task), but two sets per wavefront
@@ -862,7 +880,8 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
             cps = (int)std::max(1L, std::min((long)cps, queue_comps[queue] / (2 * mdpe::kSetComponents)));
             const int sets = (comps[p] + cps - 1) / cps, nl = P.n_layers();
             // components of like size in one set (a set's layers then fill their
-            // groups: 0.97 to 0.99 of the places taken instead of 0.87 to 0.94)
+            // groups: 0.97 to 0.99 of the places taken instead of 0.87 to 0.94),
+            // the largest in the first
             {
                 std::vector<int32_t> size(comps[p], 0), rank(comps[p]), order(comps[p]);
                 for (int32_t c : comp[p]) ++size[c];
@@ -876,27 +895,50 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
             for (int L = 1; L <= nl; ++L)
                 for (int64_t j = P.conv_off[L - 1]; j < P.conv_off[L]; ++j) at[(size_t)(comp[p][j] / cps) * nl + L]++;
             for (size_t q = 1; q < at.size(); ++q) at[q] += at[q - 1];
-            std::vector<int> to(at.begin(), at.end() - 1);
-            auto &jobs = B->set_jobs[p];
-            jobs.resize(P.conv.size());
+            auto set_groups = [&](int s) {
+                int g = 0;
+                for (int L = 0; L < nl; ++L) g += (at[(size_t)s * nl + L + 1] - at[(size_t)s * nl + L] + J - 1) / J;
+                return g;
+            };
+            // A set is a chain of dependent groups on one wavefront.  Where the
+            // largest takes longer than the queue's work spread over the XCD's
+            // wavefronts, and much longer than the layers one after the other
+            // (with a task's groups each), the instance keeps a stage per layer.
+            // Largest set against that work and against the layers, then time by
+            // sets and by layers (ms): sets kept at 1.4 and 1.3 times 3.1, 3.8 (16
+            // mixed instances), 2.5 and 1.3 times 4.4, 5.2 (32), 2.1 and 0.2 times
+            // 1.0, 2.7 (16 of 211 monomials of 1 to 12 variables, four doubles);
+            // layers kept at 3.9 and 2.7 times 2.3, 1.4, 7.2 and 2.5 times 6.4, 3.5,
+            // 91 and 1.5 times 3.3, 2.4, 61 and 2.9 times 23.6, 9.1 (16 instances of
+            // four monomials of 50 to 60 variables, d = 128, beside 120 small ones).
+            long layered = 0;
             for (int L = 1; L <= nl; ++L)
-                for (int64_t j = P.conv_off[L - 1]; j < P.conv_off[L]; ++j)
-                    jobs[to[(size_t)(comp[p][j] / cps) * nl + L - 1]++] =
-                        make_int4(P.conv[j][0], P.conv[j][1], P.conv[j][2], 0);
-            auto &groups = B->set_groups[p];
-            for (int s = 0; s < sets; ++s) {
-                const int g0 = (int)groups.size(), first = at[(size_t)s * nl], last = at[(size_t)(s + 1) * nl];
-                for (int L = 0; L < nl; ++L)
-                    for (int j = at[(size_t)s * nl + L]; j < at[(size_t)s * nl + L + 1]; j += J) groups.push_back(j);
-                emit(1, first, last - first, done_before);
-                mdpe::BatchTask &T = tmp.back().t;
-                T.group = g0;
-                T.groups = (int)groups.size() - g0;
-                tmp.back().cost = T.groups * (double)S.steps * (mdpe::batch_terms(P.m) * P.m * P.m + 10.0);
+                layered += std::min<long>(G, (P.conv_off[L] - P.conv_off[L - 1] + J - 1) / J);
+            const double step = S.steps * step_cost(P), longest = set_groups(0) * step;
+            by_sets = longest <= std::max(queue_time[queue] / mdpe::kSetComponents, mdpe::kSetOverLayers * layered * step);
+            if (by_sets) {
+                std::vector<int> to(at.begin(), at.end() - 1);
+                auto &jobs = B->set_jobs[p];
+                jobs.resize(P.conv.size());
+                for (int L = 1; L <= nl; ++L)
+                    for (int64_t j = P.conv_off[L - 1]; j < P.conv_off[L]; ++j)
+                        jobs[to[(size_t)(comp[p][j] / cps) * nl + L - 1]++] =
+                            make_int4(P.conv[j][0], P.conv[j][1], P.conv[j][2], 0);
+                auto &groups = B->set_groups[p];
+                for (int s = 0; s < sets; ++s) {
+                    const int first = at[(size_t)s * nl], last = at[(size_t)(s + 1) * nl];
+                    emit(1, first, last - first, done_before);
+                    mdpe::BatchTask &T = tmp.back().t;
+                    T.group = (int)groups.size();
+                    T.groups = set_groups(s);
+                    tmp.back().cost = T.groups * step;
+                    for (int L = 0; L < nl; ++L)
+                        for (int j = at[(size_t)s * nl + L]; j < at[(size_t)s * nl + L + 1]; j += J) groups.push_back(j);
+                }
+                groups.push_back((int)jobs.size());
+                done_before += sets;
+                ++depth;
             }
-            groups.push_back((int)jobs.size());
-            done_before += sets;
-            ++depth;
         }
         for (int L = 1; !by_sets && L <= P.n_layers(); ++L, ++depth) {
             const long a = P.conv_off[L - 1], z = P.conv_off[L];
@@ -1005,7 +1047,7 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
                 jobs_at += B->set_jobs[p].size();
                 groups_at += B->set_groups[p].size();
             }
-            B->insts[p].chains = B->d_chains[sched_index[{P.d, B->insts[p].J, B->blocks ? mdpe::batch_terms(P.m) : 0}]];
+            B->insts[p].chains = B->d_chains[sched_of[p]];
         }
         if (!(rc = alloc_copy((void **)&B->d_tasks, B->tasks.data(), B->tasks.size() * sizeof(mdpe::BatchTask))) &&
             !(rc = alloc_copy((void **)&B->d_qinfo, B->qinfo.data(), B->qinfo.size() * sizeof(int))))
