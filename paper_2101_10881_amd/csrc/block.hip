@@ -97,7 +97,7 @@ int launch_r(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipStream
     if (waves <= 3L * simds && waves > simds && 4 * bytes <= (size_t)kMaxLdsBytes)
         hipLaunchKernelGGL((conv_block_kernel<M, CORR, CX, R, U, 4>), dim3((unsigned)((waves + 3) / 4)), dim3(256),
                            4 * bytes, st, A, jobs, nj, P.d, J, pl->d_blocks, ls.stride, ls.steps, (int)bytes, Q);
-    else if (waves <= simds && waves > simds / 4)
+    else if (lone_launch(pl->most_waves, waves, simds))
         hipLaunchKernelGGL((conv_block_kernel<M, CORR, CX, R, U, 1, true>), dim3((unsigned)waves), dim3(64), bytes, st, A,
                            jobs, nj, P.d, J, pl->d_blocks, ls.stride, ls.steps, (int)bytes, Q);
     else

@@ -433,7 +433,7 @@ int launch_layer(const mdpe_plan *pl, double *A, const int4 *jobs, int nj, hipSt
             hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 4, false>), dim3((unsigned)blocks), dim3(256),
                                4 * group_bytes, st, A, jobs, nj, P.d, J,
                                pl->d_chains, P.lanes.stride, P.lanes.steps, (int)group_bytes, 1, P.simple ? 1 : 0);
-        else if (waves <= simds && waves > simds / 4)  // (fewer: room for two streams' launches)
+        else if (mdpe::lone_launch(pl->most_waves, waves, simds))
             hipLaunchKernelGGL((mdpe::conv_layer_kernel<M, CORR, CX, 1, false, false, true>), dim3((unsigned)blocks),
                                dim3(64), group_bytes, st, A, jobs, nj, P.d, J, pl->d_chains, P.lanes.stride,
                                P.lanes.steps, (int)group_bytes, 1, P.simple ? 1 : 0);
@@ -800,6 +800,7 @@ int plan_polynomial(const mdpe_poly_desc *desc, int device, mdpe_plan **out) {
         return fail(MDPE_ENOMEM, "host allocation failed while planning");
     }
     if (!err.empty()) return fail(unsupported ? MDPE_EUNSUPPORTED : MDPE_EINVAL, err);
+    pl->most_waves = mdpe::most_waves(pl->P);
     if (device >= 0) {
         int ndev = 0;
         HIP_TRY(hipGetDeviceCount(&ndev));

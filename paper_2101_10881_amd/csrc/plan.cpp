@@ -424,6 +424,36 @@ static bool blocks_pay(const Plan &P) {
 // to 1.06).
 int block_terms_of(int w, int d) { return w <= 2 || (w <= 5 && d >= 24) ? 4 : 2; }
 
+long most_waves(const Plan &P) {
+    if (P.single || P.streamed || P.fused_components > 0) return 0;
+    const LaneSchedule &ls = P.block_r > 0 ? P.blocks : P.lanes;
+    long most = 0;
+    for (int L = P.pipe_layers + 1; L <= P.n_layers(); ++L)
+        most = std::max<long>(most, (P.conv_off[L] - P.conv_off[L - 1] + ls.jobs_per_group - 1) / ls.jobs_per_group *
+                                        (long)ls.waves_per_job);
+    return most;
+}
+
+// A plan's launches all do or none does: a launch without it goes on from wherever
+// the last workgroups of the one before fell.
+// - A launch of more than a round leaves them unevenly, in this evaluation for the
+//   next or for the first of the next one (1820 products of four of sixteen
+//   variables, ten doubles, d = 31: the first layer, 910 wavefronts, 160 us with it
+//   and 278 without; five doubles, d = 63: the last one 58 and 92).  Two streams
+//   gain too (eight doubles, d = 95: 5044 and 5450 us for two evaluations).
+// - Up to a round the placement is even without it (20 workloads, 0.99 to 1.01 of
+//   the time), and it would keep two streams' launches from sharing SIMDs: two
+//   evaluations with it and without, 330 products of four of eleven variables at
+//   five doubles, d = 63, 342 and 302 us, at four, d = 95, 307 and 267; 495 of
+//   twelve at eight, d = 40, 633 and 584.
+// - Up to half a round two streams' launches fit beside each other, and it puts
+//   them there: eight and ten doubles, launches of 210 to 495, 0.77 to 0.96 of the
+//   time of two streams without it.
+// Not below a quarter of the SIMDs, which leave idle ones whatever the placement.
+bool lone_launch(long most, long waves, int simds) {
+    return waves > simds / 4 && waves <= simds && (most > simds || most <= simds / 2);
+}
+
 // Blocks of R coefficients per lane, U terms an iteration, for the staged
 // per-layer launches (conv_block.hpp) of the layers from_layer..., J jobs per
 // wavefront and Q wavefronts per job, by the estimated cycles of the layers.

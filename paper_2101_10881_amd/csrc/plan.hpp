@@ -241,6 +241,12 @@ int32_t job_components(const Plan &P, std::vector<int32_t> &comp);
 // workspace, and that `before` and `past` coefficients before and past every
 // job's second operand lie inside it.
 int block_terms_of(int w, int d);
+// Wavefronts of the largest convolution launch of a plan run layer by layer (0:
+// none is).
+long most_waves(const Plan &P);
+// Whether a launch of `waves` one-wavefront workgroups, in a plan whose largest has
+// `most`, takes one wavefront per SIMD by register count (md.hpp, one_per_simd).
+bool lone_launch(long most, long waves, int simds);
 bool small_workspace(const Plan &P);
 bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs, int before, int past);
 // The rules every plan meets (Section 5: the jobs of one layer are

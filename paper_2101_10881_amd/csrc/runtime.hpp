@@ -40,6 +40,7 @@ struct mdpe_plan {
     int *d_fblocks = nullptr;  // fused blocked convolutions: their lane schedule
     int *d_leaves = nullptr;   // addition passes: list slots
     mdpe::AddChunk *d_chunks = nullptr;  // addition passes: workgroups' parts
+    long most_waves = 0;       // mdpe::most_waves(P)
     std::vector<int64_t> add_pass;       // pass p spans d_chunks[add_pass[p] .. add_pass[p+1])
     int *d_schains = nullptr;  // single launch: the lane schedule of its job groups
 };
