@@ -1090,6 +1090,47 @@ static bool choose_chain_launch(Plan &P, bool forced, double other) {
     return forced || best + rest < 0.9 * other;
 }
 
+// Whether the chain launch of C pays so much against the plan P without it that C
+// takes more workspace than the allocation-free entry has, where P fits (callers of
+// that entry pass MDPE_NO_CHAIN_LAUNCH): chains of 16 products or more, a quarter
+// of the convolutions or more, under 0.9 of P by an estimate that favours P -- steps
+// of the coefficient schedules, one chain per CU, four to sixteen wavefronts sharing
+// its SIMDs at eff of their lone speed, one double's chain steps at 0.55 of the
+// layers' (261 monomials of 15 variables, exponents to 2, five doubles, d = 130,
+// 62.8 -> 67.9 MiB: 3080 -> 1790 us).
+static bool outgrowing_pays(const Plan &P, const Plan &C) {
+    const int Lmax = C.pipe_layers, chains = (int)C.pipe_comps.size();
+    if (P.n_layers() < 16 || Lmax < 16 || 4 * C.pipe_jobs.size() < C.conv.size()) return false;
+    const int B = (int)std::min<long>(std::max(Lmax, 2), (98304 - (long)sizeof(JobOffsets) * Lmax) /
+                                                             ((long)(P.d + 1) * P.w * 8));
+    if (B < 2) return false;
+    auto layers = [](const Plan &Q, int from) {
+        const int q = Q.lanes.waves_per_job, J = Q.lanes.jobs_per_group;
+        return Q.simple ? layer_cost(Q, q, J, dealt_steps(Q.d, J, q), Q.w == 1 ? 0.15 : 0.4, from)
+                        : layer_cost(Q, q, J, Q.lanes.steps, 1.0, from);
+    };
+    double other = layers(P, 1);
+    if (fuse_by_default(P)) {
+        const LaneSchedule one = make_lane_schedule(P.d, 1);
+        other = std::min(other, P.n_layers() * (prefer_simple_dealing(P.d, 1, P.w, one.steps)
+                                                    ? dealt_steps(P.d, 1) * (P.w == 1 ? 0.15 : 0.5)
+                                                    : (double)one.steps));
+    }
+    static const double eff[2][5] = {{1.0, 1.0, 0.80, 0.73, 0.70}, {1.0, 1.0, 0.89, 0.81, 0.74}};
+    const double rounds = std::ceil(chains / (kSimds / 4.0));
+    double best = -1;
+    for (int W : {4, 8, 12, 16})
+        for (int S : {1, 2, 4}) {
+            if (W == 16 && P.w > 8) continue;
+            std::vector<int32_t> codes;
+            int stride = 0;
+            const int k = W / 4, steps = make_chain_schedule(Lmax, P.d, W, S, B, codes, &stride);
+            const double c = rounds * steps * k * eff[P.w >= 8][k] * (1.0 + 0.08 / S) * (P.w == 1 ? 0.55 : 1.0);
+            if (best < 0 || c < best) best = c;
+        }
+    return best + layers(C, Lmax + 1) < 0.9 * other;
+}
+
 // ----------------------------------------------------------- single launch
 // FP64 instructions of one md_add / md_mul of the specification (two_sum = 6
 // additions, two_prod = 1 mul + 1 fma; the closed forms of the accounting).
@@ -1219,10 +1260,10 @@ static std::string build_plan_launches(int n, int N, int d, int m, const int32_t
         std::string e2 = build_plan_mode(n, N, d, m, nvars, vars, exps, flags, false, true, C, &uns);
         if (e2.empty() && choose_chain_launch(C, chain_forced, other)) {
             // (a plan that the allocation-free entry takes without the chain launch's
-            // fresh slots is not made too large for it)
+            // fresh slots is not made too large for it, unless long chains pay)
             auto bytes = [](const Plan &Q) { return Q.n_series * (int64_t)(Q.d + 1) * Q.w * (int64_t)sizeof(double); };
             const bool outgrows = bytes(P) <= kScratchBytes && bytes(C) > kScratchBytes;
-            if (chain_forced || !outgrows) {
+            if (chain_forced || !outgrows || outgrowing_pays(P, C)) {
                 auto h = check_hazards(C);
                 if (!h.empty()) return "internal planner error (chain launch): " + h;
                 P = std::move(C);
