@@ -992,6 +992,23 @@ static bool make_chain_plan(Plan &P, const std::vector<std::vector<int64_t>> &ch
     return true;
 }
 
+// What chains of one or two wavefronts cost beyond chain_cost's terms.  Once a CU
+// holds more of those wavefronts than SIMDs they spread unevenly: the fullest SIMD
+// counts, and with two a little more (522 chains of 28, five doubles, d = 130: 2575
+// us on two wavefronts each, 1781 on four, where the terms say 1964 and 2116; 620
+// chains of 39, four doubles, d = 80: 1144 and 740; of 160 plans 155 then take a
+// width within 5% of the best, 140 without this).  Not at one double, whose waits
+// leave the SIMDs room (708 chains of 25, d = 100: 96 us on two, 108 on four).
+// Long products lose a little more on two (226 chains of 23 at eight doubles, d =
+// 15: 227 and 207 us on four, a tie by the terms).
+static double narrow_chains(const Plan &P, size_t chains, int W) {
+    const long cus = kSimds / 4;
+    const double k = std::min(16L / W, ((long)chains + cus - 1) / cus) * W / 4.0;
+    const bool even = W >= 4 || k <= 1 || P.w == 1;
+    return (even ? 1.0 : std::max(1.0, 0.95 * (std::ceil(k) + (W == 2 ? 0.5 : 0.0)) / k)) *
+           (W == 2 && P.w >= 8 ? 1.1 : 1.0);
+}
+
 // Estimated cycles of the chain launch: its iterations, and a barrier's wait for
 // the slowest of W wavefronts (measured on p2: quad double, d = 64, 320
 // iterations on 8 wavefronts 348 us; penta double, d = 37, 222 on 4 245 us).
@@ -1002,18 +1019,17 @@ static double chain_cost(const Plan &P, size_t chains, int R, int U, int W, int 
     const long per_cu = std::min(fit, ((long)chains + cus - 1) / cus);
     const double rounds = std::ceil(chains / (double)(cus * per_cu));
     const double k = std::max(1.0, per_cu * W / 4.0);  // wavefronts per SIMD
-    // (fewer than four, long products: 226 chains of 23 at eight doubles, d = 15,
-    // took 227 us on two wavefronts and 207 on four where the terms above tie)
-    const double few = W < 4 && P.w >= 8 ? 1.1 : 1.0;
     // With a chain per CU at most and from five doubles on, whose products hold
     // independent sums, a lone wavefront issues every 5 cycles or so: four
     // wavefronts, not eight, for chains of 23 to 64 (d = 49: 10 doubles 907
-    // against 1072 us, 8 538 against 606, 5 209 against 227).  With more chains
+    // against 1072 us, 8 538 against 606, 5 209 against 227); eight for longer series
+    // up to eight doubles (28 chains of 25, 8 doubles, d = 176: 4605 on four, 4354;
+    // 180 of 27, complex quad double, d = 146: 2880 and 2653).  With more chains
     // the estimate of the rounds, made for equal chains, is the larger error and
     // keeps the factor of the narrow ones (211 monomials of 1 to 12 variables,
     // 8 doubles, d = 70: 693 us; with this factor 1146).
-    const double lone = chains > (size_t)cus || P.w < 5 ? 1.5 : P.w == 5 ? 1.2 : 1.12;
-    return few * rounds * steps * (block_iteration(P, R, U, k, lone) + (W > 1 ? (60.0 + 30.0 * W) / S : 0));
+    const double lone = chains > (size_t)cus || P.w < 5 ? 1.5 : P.w <= 8 ? 1.2 : 1.12;
+    return narrow_chains(P, chains, W) * rounds * steps * (block_iteration(P, R, U, k, lone) + (W > 1 ? (60.0 + 30.0 * W) / S : 0));
 }
 
 // The chain launch for a plan without in-place jobs: the cheapest estimate
@@ -1087,7 +1103,7 @@ static bool choose_chain_launch(Plan &P, bool forced, double other) {
     }
     if (best < 0 || !make_chain_plan(P, chains, br, bu, bw, bs, bb)) return false;
     const double rest = layers_cost(P, P.pipe_layers + 1);
-    return forced || best + rest < 0.9 * other;
+    return forced || best / narrow_chains(P, chains.size(), bw) + rest < 0.9 * other;
 }
 
 // Whether the chain launch of C pays so much against the plan P without it that C
