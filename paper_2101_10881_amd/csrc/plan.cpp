@@ -1052,8 +1052,10 @@ static bool choose_chain_launch(Plan &P, bool forced, double other) {
         members += (long)c.size();
     }
     if (!forced && (Lmax < 9 || (Lmax < 16 && chains.size() < 64) || 4 * members < (long)P.conv.size())) return false;
-    // (one double per coefficient beyond d = 160 keeps the layered plan unless asked)
-    if (!forced && P.w == 1 && P.d > 160) return false;
+    // (one double per coefficient beyond d = 190 keeps its layers unless asked; the
+    // chain launch wins on both sides of that line, p2 at d = 161, 176, 185 and 191
+    // 200, 213, 224 and 232 us against 545 to 568)
+    if (!forced && P.w == 1 && P.d > 190) return false;
     double best = -1;
     int br = 0, bu = 0, bw = 0, bs = 0, bb = 0;
     // by coefficients (R = 0, the 64-bit addresses) where the workspace is 4 GiB or more
