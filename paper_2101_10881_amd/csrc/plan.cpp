@@ -1272,7 +1272,16 @@ static std::string build_plan_launches(int n, int N, int d, int m, const int32_t
     }
     if (!P.streamed && !(flags & (kFusedLayers | kLayerLaunches | kNoChainLaunch)) &&
         (chain_forced || (P.n_layers() >= 9 && longest >= 9))) {
-        const double other = layers_cost(P, 1);
+        double other = layers_cost(P, 1);
+        // ... or, at one double, of the fused launch with a launch less than the chain
+        // launch and its layers: 0.65 us a layer and 0.05 a degree (33 plans of 9 to
+        // 33 layers at d = 3 to 8, 18 to 39 us with it: 199 monomials of 2 to 9
+        // variables, d = 3, 17.8 us, 25.7 by the chain launch; from two doubles on the
+        // chain launch is faster in 326 plans of 326)
+        if (P.w == 1 && fuse_by_default(P)) {
+            Plan F = P;
+            if (fuse_layers(F) <= 4) other = std::min(other, P.n_layers() * (1530.0 + 118.0 * d) / 0.9);
+        }
         Plan C;
         bool uns = false;
         std::string e2 = build_plan_mode(n, N, d, m, nvars, vars, exps, flags, false, true, C, &uns);
