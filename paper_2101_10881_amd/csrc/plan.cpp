@@ -30,7 +30,6 @@
 
 #include <algorithm>
 #include <numeric>
-#include <set>
 #include <unordered_map>
 
 namespace mdpe {
@@ -467,7 +466,13 @@ static void choose_block_lanes(Plan &P, int from_layer) {
     if (!blocks_pay(P)) return;
     const int w = P.w;
     const int maxq = P.lanes.waves_per_job > 1 ? 4 : 1;
-    double best = -1;
+    // candidates with the least a schedule of theirs can cost: its items fill the
+    // lanes, and the longest runs whole on one
+    struct Cand {
+        double bound;
+        int R, U, J, Q;
+    };
+    std::vector<Cand> cands;
     for (int R : {1, 4}) {
         const int U = block_terms_of(w, P.d);
         if (R == 4 && w > 1) continue;
@@ -478,20 +483,32 @@ static void choose_block_lanes(Plan &P, int from_layer) {
                                            reads_inside(P, P.corr, 0, U - 1)))
             continue;
         const long longest = P.d / U + 1, items = P.d / R + 1;
+        long all = 0;  // a job's iterations
+        for (int k = 0; k <= P.d; k += R) all += k / U + 1;
         for (int J : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64}) {
             if (block_group_bytes(P.d + 1, w, U, J) > kLdsBudget && J > 1) break;
             if (block_group_bytes(P.d + 1, w, U, J) > kMaxLdsBytes) break;
             if ((long)(J - 1) * items * (longest + 1) / 2 > (long)kLanes * (longest + 1)) break;
             for (int Q = 1; Q <= (J == 1 ? maxq : 1); ++Q) {
-                LaneSchedule ls = make_block_schedule(P.d, R, U, J, Q);
-                const double c = block_cost(P, R, U, ls, from_layer);
-                if (best < 0 || c < best) {
-                    best = c;
-                    P.blocks = std::move(ls);
-                    P.block_r = R;
-                    P.block_u = U;
-                }
+                LaneSchedule least;
+                least.jobs_per_group = J;
+                least.waves_per_job = Q;
+                least.steps = (int)std::max((J * all + kLanes * Q - 1) / (kLanes * Q), longest);
+                cands.push_back({block_cost(P, R, U, least, from_layer), R, U, J, Q});
             }
+        }
+    }
+    std::stable_sort(cands.begin(), cands.end(), [](const Cand &a, const Cand &b) { return a.bound < b.bound; });
+    double best = -1;
+    for (const Cand &c : cands) {
+        if (best >= 0 && c.bound >= best) break;
+        LaneSchedule ls = make_block_schedule(P.d, c.R, c.U, c.J, c.Q);
+        const double cost = block_cost(P, c.R, c.U, ls, from_layer);
+        if (best < 0 || cost < best) {
+            best = cost;
+            P.blocks = std::move(ls);
+            P.block_r = c.R;
+            P.block_u = c.U;
         }
     }
 }
@@ -763,7 +780,58 @@ static bool fuse_by_default(const Plan &P) {
 
 static inline int chain_window(int it, int S) { return it >= 0 ? it / S : -1; }
 
-int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> &codes, int *stride, int U) {
+// The lanes of a chain's workgroup by the iteration from which they are free:
+// an ascending list per iteration and a bit per iteration that has one.
+class FreeLanes {
+  public:
+    explicit FreeLanes(int lanes) : next_(lanes) {
+        for (int q = lanes - 1; q >= 0; --q) put(0, q);
+    }
+    // the first lane of the latest iteration up to `at`, else of the earliest one
+    std::pair<int, int> take(int at) {
+        int t = last_up_to(at);
+        if (t < 0) t = first_from(at + 1);
+        const int q = head_[t];
+        if ((head_[t] = next_[q]) < 0) bits_[t >> 6] &= ~(1ull << (t & 63));
+        return {t, q};
+    }
+    void put(int t, int q) {
+        if (t >= (int)head_.size()) {
+            head_.resize(t / 64 * 64 + 64, -1);
+            bits_.resize(head_.size() / 64, 0);
+        }
+        int *at = &head_[t];
+        while (*at >= 0 && *at < q) at = &next_[*at];
+        next_[q] = *at;
+        *at = q;
+        bits_[t >> 6] |= 1ull << (t & 63);
+        latest_ = std::max(latest_, t);
+    }
+    int latest() const { return latest_; }
+
+  private:
+    int last_up_to(int t) const {
+        t = std::min(t, (int)head_.size() - 1);
+        for (int w = t >> 6; w >= 0; --w) {
+            const uint64_t x = w == t >> 6 ? bits_[w] & (~0ull >> (63 - (t & 63))) : bits_[w];
+            if (x) return 64 * w + 63 - __builtin_clzll(x);
+        }
+        return -1;
+    }
+    int first_from(int t) const {
+        for (int w = t >> 6;; ++w) {  // (every lane is in some list)
+            const uint64_t x = w == t >> 6 ? bits_[w] & (~0ull << (t & 63)) : bits_[w];
+            if (x) return 64 * w + __builtin_ctzll(x);
+        }
+    }
+    std::vector<int> head_, next_;
+    std::vector<uint64_t> bits_;
+    int latest_ = 0;
+};
+
+// The iterations of make_chain_schedule's schedule, and its lists when `lists`
+// is not null.
+static int place_chain(int L, int d, int W, int S, int B, int U, std::vector<std::vector<int32_t>> *lists) {
     // Jobs in chain order, each job's coefficients longest first; each at the
     // earliest step its first operand allows (every x_i read after the window
     // of its store by the previous job; its own store into the LDS slot of
@@ -771,47 +839,44 @@ int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> 
     // earlier), on the lane free by then with the least idle time before it,
     // else on the lane that frees first.
     const int lanes = kLanes * W, d1 = d + 1;
-    std::set<std::pair<int, int>> lane_free;  // (free from, -lane)
-    for (int q = 0; q < lanes; ++q) lane_free.insert({0, -q});
-    std::vector<std::vector<int32_t>> lists(lanes);
-    std::vector<int> store((size_t)L * d1, 0), ready(d1);
+    FreeLanes lane_free(lanes);
+    if (lists) lists->assign(lanes, {});
+    std::vector<int> store(d1, 0), ready(d1);  // (store: the previous job's)
     std::vector<int> last_read(L, -1);
     for (int l = 0; l < L; ++l) {
         // ready[k]: the earliest start of coefficient k by its first operand
         for (int k = 0; k <= d; ++k) {
             ready[k] = k > 0 ? ready[k - 1] : 0;
-            if (l > 0)
-                ready[k] = std::max(ready[k], S * (chain_window(store[(size_t)(l - 1) * d1 + k], S) + 1) - k / U + 1);
+            if (l > 0) ready[k] = std::max(ready[k], S * (chain_window(store[k], S) + 1) - k / U + 1);
         }
+        const bool reuses = l + 1 < L && l + 1 - B >= 0;
+        const int from_slot = reuses ? S * (chain_window(last_read[l + 1 - B], S) + 1) : 0;
         for (int k = d; k >= 0; --k) {
-            int s0 = ready[k];
-            if (l + 1 < L && l + 1 - B >= 0) s0 = std::max(s0, S * (chain_window(last_read[l + 1 - B], S) + 1) - k / U);
-            auto it = lane_free.upper_bound({s0, 1});
-            if (it != lane_free.begin()) {
-                --it;  // the latest free time up to s0, its first lane
-            } else {
-                it = lane_free.begin();
-                const int t = it->first;  // the earliest free time, its first lane
-                it = std::prev(lane_free.upper_bound({t, 1}));
-            }
-            const int from = it->first, best = -it->second;
-            lane_free.erase(it);
+            const int s0 = reuses ? std::max(ready[k], from_slot - k / U) : ready[k];
+            const auto [from, lane] = lane_free.take(s0);
             const int start = std::max(s0, from);
-            for (int g = start - from; g > 0;) {
-                const int q = std::min(g, 0x10000);
-                lists[best].push_back((kIdleJob << 16) | (q - 1));
-                g -= q;
+            if (lists) {
+                auto &list = (*lists)[lane];
+                for (int g = start - from; g > 0;) {
+                    const int q = std::min(g, 0x10000);
+                    list.push_back((kIdleJob << 16) | (q - 1));
+                    g -= q;
+                }
+                list.push_back((l << 16) | k);
             }
-            lists[best].push_back((l << 16) | k);
-            lane_free.insert({start + k / U + 1, -best});
-            store[(size_t)l * d1 + k] = start + k / U;
+            lane_free.put(start + k / U + 1, lane);
+            store[k] = start + k / U;
             last_read[l] = std::max(last_read[l], start + k / U - 1);
         }
     }
     // a multiple of the window, and even (the kernel may run two steps per iteration)
     const int q = S % 2 ? 2 * S : S;
-    int steps = lane_free.rbegin()->first;
-    steps = (steps + q - 1) / q * q;
+    return (lane_free.latest() + q - 1) / q * q;
+}
+
+int make_chain_schedule(int L, int d, int W, int S, int B, std::vector<int32_t> &codes, int *stride, int U) {
+    std::vector<std::vector<int32_t>> lists;
+    const int lanes = kLanes * W, steps = place_chain(L, d, W, S, B, U, &lists);
     size_t st = 1;
     for (auto &x : lists) st = std::max(st, x.size() + 1);
     *stride = (int)st;
@@ -848,6 +913,23 @@ std::string check_chain_schedule(int L, int d, int W, int S, int B, int steps, c
     }
     for (int v : start)
         if (v < 0) return "coefficient never scheduled";
+    // x_i of job l is read by its coefficients k >= i: the earliest of them starts
+    // after the barrier that follows its store, the latest before the one after
+    // which it is overwritten
+    bool ordered = true;
+    for (int l = 0; l < L && ordered; ++l) {
+        const int wj = l - 1 + B;  // stores the first operand of job l + B into the same slot
+        int first = start[(size_t)l * d1 + d], last = first;
+        for (int i = d; i >= 0; --i) {
+            first = std::min(first, start[(size_t)l * d1 + i]);
+            last = std::max(last, start[(size_t)l * d1 + i]);
+            auto stored = [&](int job) { return chain_window(start[(size_t)job * d1 + i] + i / U, S); };
+            ordered &= !(l > 0 && chain_window(first + i / U - 1, S) <= stored(l - 1)) &&
+                       !(wj + 1 < L && stored(wj) <= chain_window(last + i / U - 1, S));
+        }
+    }
+    if (ordered) return "";
+    // (which one is not)
     for (int l = 0; l < L; ++l)
         for (int k = 0; k <= d; ++k) {
             const int s = start[(size_t)l * d1 + k];
@@ -1056,8 +1138,15 @@ static bool choose_chain_launch(Plan &P, bool forced, double other) {
     // chain launch wins on both sides of that line, p2 at d = 161, 176, 185 and 191
     // 200, 213, 224 and 232 us against 545 to 568)
     if (!forced && P.w == 1 && P.d > 190) return false;
-    double best = -1;
-    int br = 0, bu = 0, bw = 0, bs = 0, bb = 0;
+    // candidates with the least their schedule can cost: its iterations fill the
+    // lanes, and a product's first coefficient starts a barrier after the one
+    // before it is stored
+    struct Cand {
+        double bound;
+        int R, U, W, S, B;
+        long lds;
+    };
+    std::vector<Cand> cands;
     // by coefficients (R = 0, the 64-bit addresses) where the workspace is 4 GiB or more
     const bool small = small_workspace(P);
     // (four terms of one coefficient: 0.63 to 1.0 on p2, 1.05 at best)
@@ -1067,6 +1156,8 @@ static bool choose_chain_launch(Plan &P, bool forced, double other) {
         if (small ? R == 0 : R > 0) continue;
         if ((R == 4 && P.w > 2) || (R == 2 && P.w > 5) || (R == 1 && U == 2 && P.w > 10)) continue;
         if (U > 1 && !reads_inside(P, P.conv, R == 1 ? U - 1 : 0, R == 1 ? 0 : U - 1)) continue;
+        const int items = P.d / r1, tail = R == 1 ? P.d / u1 + 1 : items + 1;
+        const long all = R == 1 ? (long)tail * (P.d + 1 - (tail - 1) * (long)u1 / 2) : (long)tail * (tail + 1) / 2;
         int last_B = 0;
         for (long budget : {98304L, 49152L, 24576L}) {
             const int B = (int)std::min<long>(std::max(Lmax, 2), (budget - (long)sizeof(JobOffsets) * Lmax) /
@@ -1082,25 +1173,29 @@ static bool choose_chain_launch(Plan &P, bool forced, double other) {
                 if (W < 4 && (R == 0 || chains.size() < 64)) continue;
                 for (int S : {1, 2, 4}) {
                     if (W == 1 && S > 1) continue;
-                    // (not worth a schedule if its fewest iterations cost more than the best)
-                    const int items = P.d / r1, tail = R == 1 ? P.d / u1 + 1 : items + 1;
-                    const long all = R == 1 ? (long)tail * (P.d + 1 - (tail - 1) * (long)u1 / 2) : (long)tail * (tail + 1) / 2;
-                    const int fewest = (int)std::max(Lmax * all / (kLanes * W), (long)Lmax - 1 + tail);
-                    if (best >= 0 && chain_cost(P, chains.size(), r1, u1, W, S, fewest, lds) >= best) continue;
-                    std::vector<int32_t> cs;
-                    int stride = 0;
-                    const int steps = make_chain_schedule(Lmax, P.d / r1, W, S, B, cs, &stride, R == 1 ? U : 1);
-                    const double c = chain_cost(P, chains.size(), r1, u1, W, S, steps, lds);
-                    if (best < 0 || c < best) {
-                        best = c;
-                        br = R;
-                        bu = U;
-                        bw = W;
-                        bs = S;
-                        bb = B;
-                    }
+                    int start = 0;
+                    for (int l = 1; l < Lmax; ++l) start = S * (start / S + 1) + 1;
+                    const int fewest = (int)std::max(Lmax * all / (kLanes * W), (long)start + tail);
+                    cands.push_back({chain_cost(P, chains.size(), r1, u1, W, S, fewest, lds), R, U, W, S, B, lds});
                 }
             }
+        }
+    }
+    // the cheapest, schedules made in the order of the bounds until none can be cheaper
+    std::stable_sort(cands.begin(), cands.end(), [](const Cand &a, const Cand &b) { return a.bound < b.bound; });
+    double best = -1;
+    int br = 0, bu = 0, bw = 0, bs = 0, bb = 0;
+    for (const Cand &c : cands) {
+        if (best >= 0 && c.bound >= best) break;
+        const int steps = place_chain(Lmax, P.d / std::max(c.R, 1), c.W, c.S, c.B, c.R == 1 ? c.U : 1, nullptr);
+        const double cost = chain_cost(P, chains.size(), std::max(c.R, 1), std::max(c.U, 1), c.W, c.S, steps, c.lds);
+        if (best < 0 || cost < best) {
+            best = cost;
+            br = c.R;
+            bu = c.U;
+            bw = c.W;
+            bs = c.S;
+            bb = c.B;
         }
     }
     if (best < 0 || !make_chain_plan(P, chains, br, bu, bw, bs, bb)) return false;
@@ -1140,9 +1235,7 @@ static bool outgrowing_pays(const Plan &P, const Plan &C) {
     for (int W : {4, 8, 12, 16})
         for (int S : {1, 2, 4}) {
             if (W == 16 && P.w > 8) continue;
-            std::vector<int32_t> codes;
-            int stride = 0;
-            const int k = W / 4, steps = make_chain_schedule(Lmax, P.d, W, S, B, codes, &stride);
+            const int k = W / 4, steps = place_chain(Lmax, P.d, W, S, B, 1, nullptr);
             const double c = rounds * steps * k * eff[P.w >= 8][k] * (1.0 + 0.08 / S) * (P.w == 1 ? 0.55 : 1.0);
             if (best < 0 || c < best) best = c;
         }
@@ -1284,7 +1377,8 @@ static std::string build_plan_launches(int n, int N, int d, int m, const int32_t
         }
         Plan C;
         bool uns = false;
-        std::string e2 = build_plan_mode(n, N, d, m, nvars, vars, exps, flags, false, true, C, &uns);
+        // (at its earliest layers: make_chain_plan orders the jobs anew)
+        std::string e2 = build_plan_mode(n, N, d, m, nvars, vars, exps, flags | kAsapLayers, false, true, C, &uns);
         if (e2.empty() && choose_chain_launch(C, chain_forced, other)) {
             // (a plan that the allocation-free entry takes without the chain launch's
             // fresh slots is not made too large for it, unless long chains pay)
