@@ -14,8 +14,6 @@ namespace mdpe {
 constexpr int kAddThreads = 256;
 constexpr int kAddCoefs = 16;                        // coefficients of a workgroup
 constexpr int kAddRuns = kAddThreads / kAddCoefs;    // runs of leaves of a workgroup
-// leaves a thread sums in registers
-__host__ __device__ constexpr int add_run(int w) { return w <= 8 ? 8 : 4; }
 
 // A workgroup sums parts blockIdx.x, + gridDim.x, .. of a pass at the 16
 // coefficients of blockIdx.y: thread (run, c) the subtree of its run of E
@@ -97,7 +95,7 @@ __global__ __launch_bounds__(kAddThreads) void add_tree_kernel(double *__restric
     }
 }
 
-int add_pass_cover(int w) { return kAddRuns * add_run(w); }
+static_assert(kAddRuns * add_run(1) == add_pass_leaves(1), "a part's leaves");
 
 template <int M, bool CX>
 static void launch(const mdpe_plan *pl, int p, double *A, double *value, double *grad, hipStream_t st) {

@@ -100,7 +100,7 @@ __device__ __forceinline__ int xcd_id() { return (int)(__builtin_amdgcn_s_getreg
 __host__ __device__ constexpr int batch_terms(int w) { return w <= 3 ? 4 : 2; }
 
 // An addition task by passes: each lane sums one part of an output's list (up to
-// add_pass_cover leaves) at one coefficient, E elements at a time with their
+// add_pass_leaves leaves) at one coefficient, E elements at a time with their
 // loads in flight together, in the pairs of the tree (an element's sum stands in
 // its last leaf's slot, as the level-by-level additions leave it; a lane reads
 // back only what it stored itself).  A launch stage per tree level cost a
@@ -948,7 +948,7 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         }
         // additions by passes over parts of the lists (plan's chunks), a task for
         // about add_items_per_task additions of coefficients
-        const mdpe::AddPasses passes = B->blocks ? mdpe::make_add_passes(P, mdpe::add_pass_cover(P.w)) : mdpe::AddPasses();
+        const mdpe::AddPasses passes = B->blocks ? mdpe::make_add_passes(P, mdpe::add_pass_leaves(P.w)) : mdpe::AddPasses();
         const bool by_passes = B->blocks && (long)passes.chunks.size() * d1 < INT32_MAX;
         if (by_passes) {
             long done = 0;  // additions in the tasks so far: a task's `first` and `count` number them

@@ -825,7 +825,7 @@ int plan_polynomial(const mdpe_poly_desc *desc, int device, mdpe_plan **out) {
         std::vector<int2> add(P.add.size()), stage(P.stage.size());
         for (size_t q = 0; q < P.add.size(); ++q) add[q] = make_int2(P.add[q][0], P.add[q][1]);
         for (size_t q = 0; q < P.stage.size(); ++q) stage[q] = make_int2(P.stage[q][0], P.stage[q][1]);
-        const mdpe::AddPasses passes = mdpe::make_add_passes(P, mdpe::add_pass_cover(P.w));
+        const mdpe::AddPasses passes = mdpe::make_add_passes(P, mdpe::add_pass_leaves(P.w));
         pl->add_pass = passes.off;
         int rc;
         mdpe_plan *raw = pl.get();

@@ -1258,13 +1258,19 @@ static long md_instr(bool mul, int m) {
     return 6 * (tse + tsp + rs) + plain + (ntp + 1) + (ntp + 2 * (m - 1));
 }
 
-// Estimated microseconds of a plan's evaluation: per-launch (the kernel
-// boundary of ~4.5 us between dependent launches, measured on MI355X, plus
-// each launch's rounds of the SIMDs) against one workgroup of `waves`
-// wavefronts that runs every stage.  A multiply-add step of one wavefront
-// costs its md instructions plus ~50 of bookkeeping, 4 cycles each at
-// ~2.2 GHz; a wavefront sharing its SIMD with k-1 others takes k times as
-// long.  Dealt coefficients (w <= 2) take the measured weight of their steps.
+// Estimated microseconds of a plan's evaluation layer by layer and in one
+// workgroup of `waves` wavefronts that runs every stage.  The coefficients fit 257
+// and 266 small plans measured so (2 to 150 monomials of 1 to 8 variables, one to
+// ten doubles, d = 1 to 48; errors of 12 and 20%):
+// - by layers, 3.3 us and 2.2 a launch (staging, each layer, each addition pass), 1.6
+//   more for a layer of one double, 0.73 of the layers' estimated cycles at 2.35
+//   GHz, and 0.53 ns an instruction of an addition for each level of the deepest tree;
+// - in one workgroup, its rounds of convolutions at 1.48 of their estimate (a
+//   multiply-add step costs its md instructions and ~50 of bookkeeping, 4 cycles
+//   each at 2.2 GHz, a wavefront sharing its SIMD with k - 1 others k times as
+//   long; dealt coefficients of w <= 2 take the measured weight of their steps),
+//   1 us and 12 ns an instruction for each of its rounds of additions, 0.47 us a
+//   phase, 2.4 us a round of scalings.
 struct SingleCost {
     double multi_us, single_us;
     int waves;
@@ -1278,24 +1284,21 @@ static SingleCost single_launch_cost(const Plan &P) {
     const long add = (cx ? 2 : 1) * md_instr(false, P.m);
     const double step_us = (double)(mul + add + 50) * 4 / 2200.0;
     const double add_us = (double)(add + 20) * 4 / 2200.0;
-    const double boundary_us = 4.5;
     const long d1 = P.d + 1;
     SingleCost c{0, 0, 0, LaneSchedule(), false};
-    // per launch
-    const int J = P.lanes.jobs_per_group, Q = P.lanes.waves_per_job;
-    const double lsteps = P.simple ? dealt_steps(P.d, J, Q) * (P.w == 1 ? 0.15 : 0.4) : (double)P.lanes.steps;
-    long launches = 2 + P.n_layers() + P.n_levels() + (P.scale.empty() ? 0 : 1);
-    c.multi_us = launches * boundary_us;
-    for (int L = 1; L <= P.n_layers(); ++L) {
-        const long waves = (P.conv_off[L] - P.conv_off[L - 1] + J - 1) / J * Q;
-        c.multi_us += std::ceil(waves / (double)kSimds) * lsteps * step_us;
-    }
-    for (int r = 1; r <= P.n_levels(); ++r) {
-        const long items = (P.add_off[r] - P.add_off[r - 1]) * d1;
-        c.multi_us += std::ceil(items / (256.0 * kSimds)) * add_us;
-    }
-    // one workgroup: the cheapest of 4, 8 and 16 wavefronts, one-wavefront
+    // by layers
+    const int nl = P.n_layers(), cover = add_pass_leaves(P.w);
+    int64_t longest = 0;
+    for (size_t o = 0; o + 1 < P.list_off.size(); ++o) longest = std::max(longest, P.list_off[o + 1] - P.list_off[o]);
+    int passes = 1;
+    for (int64_t l = longest; l > cover; l = (l + cover - 1) / cover) ++passes;
+    const int launches = 1 + nl + passes + (P.scale.empty() ? 0 : 1);
+    c.multi_us = 3.3 + 2.2 * launches + (P.w == 1 ? 1.6 * nl : 0.0) +
+                 0.73 * (layers_cost(P, 1) - 10000.0 * nl) / 2350.0 +
+                 0.00053 * std::ceil(std::log2(std::max<double>((double)longest, 2.0))) * add;
+    // one workgroup: 4, 8 or 16 wavefronts (the cheapest by the sum below), one-wavefront
     // groups of J0 (or fewer) jobs within the LDS of the workgroup
+    double least = -1;
     c.single_us = -1;
     const long stage_items = (long)P.stage.size() * d1, gather_items = (long)(1 + P.n) * d1;
     for (int W : {4, 8, 16}) {
@@ -1307,18 +1310,18 @@ static SingleCost single_launch_cost(const Plan &P) {
                 const bool simple = prefer_simple_dealing(P.d, Js, P.w, ls.steps);
                 const double st = simple ? dealt_steps(P.d, Js) * (P.w == 1 ? 0.15 : 0.5) : (double)ls.steps;
                 const double share = W / 4.0;  // wavefronts per SIMD
-                double u = boundary_us;
-                for (int L = 1; L <= P.n_layers(); ++L) {
-                    const long jobs = P.conv_off[L] - P.conv_off[L - 1];
-                    u += std::ceil(jobs / (double)(W * Js)) * st * step_us * share + 0.5;
-                }
                 const double threads = 64.0 * W;
+                double conv = 0, adds = 0;
+                for (int L = 1; L <= nl; ++L)
+                    conv += std::ceil((P.conv_off[L] - P.conv_off[L - 1]) / (double)(W * Js)) * st * step_us * share;
                 for (int r = 1; r <= P.n_levels(); ++r)
-                    u += std::ceil((P.add_off[r] - P.add_off[r - 1]) * d1 / threads) * add_us * share + 0.5;
-                u += std::ceil((double)P.scale.size() * d1 / threads) * step_us * share;
-                u += std::ceil((stage_items + gather_items) / threads) * 0.2 + 1.0;
-                if (c.single_us < 0 || u < c.single_us) {
-                    c.single_us = u;
+                    adds += std::ceil((P.add_off[r] - P.add_off[r - 1]) * d1 / threads);
+                const double scales = std::ceil((double)P.scale.size() * d1 / threads);
+                const double u = conv + adds * add_us * share + scales * step_us * share +
+                                 std::ceil((stage_items + gather_items) / threads) * 0.2;
+                if (least < 0 || u < least) {
+                    least = u;
+                    c.single_us = 1.48 * conv + adds * (1.0 + 0.012 * add) + 0.47 * (nl + P.n_levels()) + 2.4 * scales;
                     c.waves = W;
                     c.lanes = ls;
                     c.simple = simple;
@@ -1334,7 +1337,12 @@ static SingleCost single_launch_cost(const Plan &P) {
 static bool choose_single_launch(Plan &P, bool forced) {
     if (P.streamed || P.pipe_layers > 0 || P.fused_components > 0) return false;
     const SingleCost c = single_launch_cost(P);
-    if (c.single_us < 0 || (!forced && c.single_us >= 0.7 * c.multi_us)) return false;
+    // (of 230 plans measured both ways the choice takes 1.02 times the better one's time
+    // together; below 17 us, where launches alone tie the estimates, one workgroup
+    // keeps the plans up to 1.4: 78 monomials of one or two variables, two doubles, d =
+    // 3, 13.1 us and 16.0 by layers)
+    const double most = c.multi_us < 17.0 ? 1.4 * c.multi_us : c.multi_us;
+    if (c.single_us < 0 || (!forced && c.single_us >= most)) return false;
     P.single = true;
     P.single_waves = c.waves;
     P.single_lanes = c.lanes;

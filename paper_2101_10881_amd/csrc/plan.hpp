@@ -217,6 +217,10 @@ bool prefer_simple_dealing(int d, int J, int w, int schedule_steps);
 // turn (the slowest wavefront's).
 int dealt_steps(int d, int J, int Q = 1);
 int choose_jobs_per_group(int d, int w);
+// Leaves of one workgroup's part of an addition pass: 16 runs of the leaves that a
+// thread sums in registers.
+__host__ __device__ constexpr int add_run(int w) { return w <= 8 ? 8 : 4; }
+constexpr int add_pass_leaves(int w) { return 16 * add_run(w); }
 // One workgroup's part of an addition pass: the leaves
 // leaves[first .. first+count) of one output's list.  out >= 0: the list's last
 // pass, the sum is output `out` (0 = value, 1+i = d/dz_i); else the sum goes to

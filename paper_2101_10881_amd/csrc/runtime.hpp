@@ -57,7 +57,6 @@ int launch_block_chain(const mdpe_plan *pl, double *A, hipStream_t st);
 // Pass p of the plan's addition trees; the last pass of a list writes the
 // caller's value or gradient.
 int launch_add_pass(const mdpe_plan *pl, int p, double *A, double *value, double *grad, hipStream_t st);
-int add_pass_cover(int w);  // leaves of one workgroup's part
 int simd_count(int device);
 }  // namespace mdpe
 
