@@ -771,6 +771,26 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         qload[best] += icost[p];
         B->inst_queue[p] = best;
     }
+    // Each instance's convolution layers: the plan's, or, coefficient by coefficient,
+    // of one made for the chain launch its jobs at their earliest layers (16
+    // instances of 211 monomials of 1 to 12 variables, d = 37: eight doubles 11.19 ->
+    // 9.47 ms, one 1.08 -> 1.07; by blocks one way or the other: sets of ragged
+    // instances 0.90 of the time at four doubles, deep instances dealt over the
+    // queues 1.06, 96 mixed ones of 4 to 20 variables 1.08).
+    std::vector<std::vector<std::array<int32_t, 3>>> own_conv(count);
+    std::vector<std::vector<int64_t>> own_off(count);
+    for (int p = 0; p < count; ++p)
+        if (!B->blocks && plans[p]->P.pipe_layers > 0 &&
+            !mdpe::earliest_layers(plans[p]->P, own_conv[p], own_off[p])) {
+            own_conv[p].clear();
+            own_off[p].clear();
+        }
+    auto conv_of = [&](int p) -> const std::vector<std::array<int32_t, 3>> & {
+        return own_off[p].empty() ? plans[p]->P.conv : own_conv[p];
+    };
+    auto off_of = [&](int p) -> const std::vector<int64_t> & {
+        return own_off[p].empty() ? plans[p]->P.conv_off : own_off[p];
+    };
     // Convolutions by component sets where a queue has a component for every
     // resident wavefront of its XCD (32 CUs x 8): a task then runs whole
     // components (monomials), its groups one after the other on one wavefront,
@@ -801,8 +821,9 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
                                        : mdpe::make_lane_schedule(P.d, J));
         }
         sched_of[p] = sched_index[key];
+        const auto &off = off_of(p);
         double groups = 0;
-        for (int L = 1; L <= P.n_layers(); ++L) groups += (double)((P.conv_off[L] - P.conv_off[L - 1] + J - 1) / J);
+        for (size_t L = 1; L < off.size(); ++L) groups += (double)((off[L] - off[L - 1] + J - 1) / J);
         const double t = groups * scheds[sched_of[p]].steps * step_cost(P);
         if (B->inst_queue[p] >= 0)
             queue_time[B->inst_queue[p]] += t;
@@ -870,15 +891,17 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         // stage
         done_before += items(0, (long)P.stage.size() * d1);
         ++depth;
+        const auto &conv = conv_of(p);
+        const auto &off = off_of(p);
         bool by_sets = !dealt && comps[p] > 0 && queue_comps[queue] >= mdpe::kSetComponents;
         if (by_sets) {
             // 2J components per set, so that a layer's jobs fill groups of J (a
             // tile may ask for more work per task), but two sets per wavefront
             // of the XCD
-            const double per_comp = (double)P.conv.size() / comps[p];
+            const double per_comp = (double)conv.size() / comps[p];
             int cps = std::max(2 * J, (int)((double)t.groups_per_task * J / per_comp));
             cps = (int)std::max(1L, std::min((long)cps, queue_comps[queue] / (2 * mdpe::kSetComponents)));
-            const int sets = (comps[p] + cps - 1) / cps, nl = P.n_layers();
+            const int sets = (comps[p] + cps - 1) / cps, nl = (int)off.size() - 1;
             // components of like size in one set (a set's layers then fill their
             // groups: 0.97 to 0.99 of the places taken instead of 0.87 to 0.94),
             // the largest in the first
@@ -893,7 +916,7 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
             // counting sort by (set, layer)
             std::vector<int> at((size_t)sets * nl + 1, 0);
             for (int L = 1; L <= nl; ++L)
-                for (int64_t j = P.conv_off[L - 1]; j < P.conv_off[L]; ++j) at[(size_t)(comp[p][j] / cps) * nl + L]++;
+                for (int64_t j = off[L - 1]; j < off[L]; ++j) at[(size_t)(comp[p][j] / cps) * nl + L]++;
             for (size_t q = 1; q < at.size(); ++q) at[q] += at[q - 1];
             auto set_groups = [&](int s) {
                 int g = 0;
@@ -913,17 +936,17 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
             // four monomials of 50 to 60 variables, d = 128, beside 120 small ones).
             long layered = 0;
             for (int L = 1; L <= nl; ++L)
-                layered += std::min<long>(G, (P.conv_off[L] - P.conv_off[L - 1] + J - 1) / J);
+                layered += std::min<long>(G, (off[L] - off[L - 1] + J - 1) / J);
             const double step = S.steps * step_cost(P), longest = set_groups(0) * step;
             by_sets = longest <= std::max(queue_time[queue] / mdpe::kSetComponents, mdpe::kSetOverLayers * layered * step);
             if (by_sets) {
                 std::vector<int> to(at.begin(), at.end() - 1);
                 auto &jobs = B->set_jobs[p];
-                jobs.resize(P.conv.size());
+                jobs.resize(conv.size());
                 for (int L = 1; L <= nl; ++L)
-                    for (int64_t j = P.conv_off[L - 1]; j < P.conv_off[L]; ++j)
+                    for (int64_t j = off[L - 1]; j < off[L]; ++j)
                         jobs[to[(size_t)(comp[p][j] / cps) * nl + L - 1]++] =
-                            make_int4(P.conv[j][0], P.conv[j][1], P.conv[j][2], 0);
+                            make_int4(conv[j][0], conv[j][1], conv[j][2], 0);
                 auto &groups = B->set_groups[p];
                 for (int s = 0; s < sets; ++s) {
                     const int first = at[(size_t)s * nl], last = at[(size_t)(s + 1) * nl];
@@ -940,8 +963,10 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
                 ++depth;
             }
         }
-        for (int L = 1; !by_sets && L <= P.n_layers(); ++L, ++depth) {
-            const long a = P.conv_off[L - 1], z = P.conv_off[L];
+        if (!by_sets && !own_off[p].empty())
+            for (const auto &t : conv) B->set_jobs[p].push_back(make_int4(t[0], t[1], t[2], 0));
+        for (int L = 1; !by_sets && L < (int)off.size(); ++L, ++depth) {
+            const long a = off[L - 1], z = off[L];
             int n = 0;
             for (long f = a; f < z; f += (long)G * J, ++n) emit(1, f, (int)std::min((long)G * J, z - f), done_before);
             done_before += n;

@@ -980,6 +980,28 @@ static bool find_chains(const Plan &P, std::vector<std::vector<int64_t>> &chains
     return !chains.empty();
 }
 
+bool earliest_layers(const Plan &P, std::vector<std::array<int32_t, 3>> &conv, std::vector<int64_t> &off) {
+    std::vector<int> written(P.n_series, 0);  // layer of a slot's last writer
+    std::vector<int> layer(P.conv.size());
+    int nl = 0;
+    for (size_t j = 0; j < P.conv.size(); ++j) {
+        const auto &t = P.conv[j];
+        layer[j] = std::max(written[t[0]], written[t[1]]) + 1;
+        written[t[2]] = std::max(written[t[2]], layer[j]);
+        nl = std::max(nl, layer[j]);
+    }
+    off.assign(nl + 1, 0);
+    for (int L : layer) off[L]++;
+    for (int L = 1; L <= nl; ++L) off[L] += off[L - 1];
+    std::vector<int64_t> at(off.begin(), off.end() - 1);
+    conv.resize(P.conv.size());
+    for (size_t j = 0; j < P.conv.size(); ++j) conv[at[layer[j] - 1]++] = P.conv[j];
+    Plan Q = P;
+    Q.conv = conv;
+    Q.conv_off = off;
+    return check_hazards(Q).empty();
+}
+
 // Estimated cycles of the per-layer launches of the layers from_layer...: their
 // arithmetic and ~4.5 us (10000 cycles) of launch boundary each.
 static double layers_cost(const Plan &P, int from_layer) {

@@ -241,6 +241,10 @@ struct AddPasses {
 AddPasses make_add_passes(const Plan &P, int cover);
 // The independent component of every convolution job; returns their number.
 int32_t job_components(const Plan &P, std::vector<int32_t> &comp);
+// The convolutions of a chain launch's plan at their earliest layers, for an
+// executor that runs layers: the plan's own put every chain's q-th product in layer
+// q and all other products after the chains.  False where that order is not safe.
+bool earliest_layers(const Plan &P, std::vector<std::array<int32_t, 3>> &conv, std::vector<int64_t> &off);
 // What the blocked kernels need of a plan: 32-bit byte offsets into its
 // workspace, and that `before` and `past` coefficients before and past every
 // job's second operand lie inside it.
