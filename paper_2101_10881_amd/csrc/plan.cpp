@@ -396,20 +396,26 @@ bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs
 
 // Whether the staged launches of width w and degree d run blocks.  Against the
 // coefficient-by-coefficient kernel (p1, d = 8 / 31 / 63 / 95 / 152, wall time):
-// two doubles per coefficient 1.27 / 0.99 / 1.33 / 1.18 / 1.31 times as fast
-// (one: 0.86 to 0.93 at d = 31 to 95 on p1's layers of up to 5460 jobs, 1.0 at
-// d = 128 to 191, 0.54 to 0.8 there on layers of 36 to 1100; on p3's of 16256
-// 1.22 and 1.34 at d = 32 and 64),
+// two doubles per coefficient 1.27 / 0.99 / 1.33 / 1.18 / 1.31 times as fast,
 // three 1.51 / 1.10 / 1.18 / 1.13 / 1.10, four 1.39 / 1.04 / 1.09 / 1.06 / 1.05,
 // five 1.30 / 1.02 / 1.04 / 1.02 / 0.98, eight 1.09 / 1.00 / 0.99 / 0.98 / 0.99:
 // what blocks save is the ~60 instructions a step spends around its
 // arithmetic, 1124 instructions at eight doubles, where the other kernel's
-// overlap of a product with the sum before it is worth more.
+// overlap of a product with the sum before it is worth more.  Up to d = 16 blocks
+// win from six doubles on too (six to ten, layers of 4 to 6000 jobs: 0.98 to 2.2
+// times as fast), but at eight doubles and even degrees from 12 on, whose last
+// iteration is padded, not in layers of a few lone wavefronts (4 products of two
+// variables: d = 12, 14, 16 0.96, 0.96, 0.98; 60 of three 1.00, 1.03, 0.99; 2000
+// 1.13, 0.98, 1.14).  One double: d = 32 / 64 / 100 / 128 / 152 / 191 by the largest
+// layer's jobs, 4200 0.96 / 1.14 / 0.88 / 1.16 / 1.07 / 0.86, 5000 0.99 / 1.13 /
+// 0.94 / 1.25 / 1.15 / 0.95, 6000 1.29 / 1.17 / 1.14 / 1.31 / 1.23 / 1.01, 6400 1.19
+// / 1.10 / 1.02 / 1.23 / 1.16 / 1.01: from six rounds of the SIMDs.
 static bool blocks_pay(const Plan &P) {
     if (P.streamed || !small_workspace(P)) return false;
-    if (P.w > 1) return P.w <= 4 || (P.w == 5 && P.d <= 127) || P.d <= 16;
     long most = 0;
     for (int L = 1; L <= P.n_layers(); ++L) most = std::max(most, (long)(P.conv_off[L] - P.conv_off[L - 1]));
+    if (P.m == 8 && P.w == 8 && P.d >= 12 && P.d % 2 == 0 && most <= 16) return false;
+    if (P.w > 1) return P.w <= 4 || (P.w == 5 && P.d <= 127) || P.d <= 16;
     return most > 6144;
 }
 
