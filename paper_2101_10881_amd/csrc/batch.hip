@@ -440,10 +440,12 @@ int prepare_batch(mdpe_batch *b) {
         if (per_cu > 4) per_cu -= per_cu % 4;
         // Blocked convolutions keep a SIMD busy with few wavefronts, and with
         // fewer of them every task, and so the launch's last ones, end sooner.
-        // 2, 3 and 4 per SIMD measured (ms): 64 mixed instances 6.19, 8.20,
-        // 8.10; 128 7.72, 8.36, 8.35; 256 17.2, 17.1, 17.0; 512 (64837
-        // convolution tasks) 29.1, 27.2, 28.1.
-        if (BLK) per_cu = std::min(per_cu, b->stage_tasks[1] >= 40000 ? 12 : 8);
+        // Two and three per SIMD by convolution tasks (ms; four: three or worse):
+        // two and four doubles 14687 7.08, 7.77, 28518 12.3, 12.6, 41154 18.1, 17.5,
+        // 60987 26.2, 24.7; three 19212 5.40, 5.51, 27067 7.50, 7.46, 37609 10.2, 10.1;
+        // five 14124 3.10, 3.30, 21203 4.57, 4.58, 30663 6.70, 6.62; four, of 4 to 12
+        // variables, 16731 25.4, 25.6, 32612 49.8, 47.6.
+        if (BLK) per_cu = std::min(per_cu, b->stage_tasks[1] >= 30000 ? 12 : 8);
         b->grid = std::max(1, per_cu) * cus;
     }
     return MDPE_OK;
