@@ -56,7 +56,7 @@ typedef struct {
     uint32_t flags;         /* 0, or MDPE_KEEP_MONOMIAL_VALUES, MDPE_COMPLEX, MDPE_STREAM_OPERANDS,
                                MDPE_STAGE_OPERANDS, MDPE_ASAP_LAYERS, MDPE_FUSED_LAYERS,
                                MDPE_LAYER_LAUNCHES, MDPE_CHAIN_LAUNCH, MDPE_NO_CHAIN_LAUNCH,
-                               MDPE_SINGLE_LAUNCH */
+                               MDPE_SINGLE_LAUNCH, MDPE_WIDE_OFFSETS */
     const int32_t *exps;    /* host [sum n_k] exponents in 1..64 aligned with vars, or NULL
                                (every exponent one).  Monomial k is then
                                a_k prod_j z_{i_j}^{e_j}: Section 3 writes it as the
@@ -171,6 +171,11 @@ typedef struct {
  * MDPE_FUSED_LAYERS, MDPE_LAYER_LAUNCHES, MDPE_STREAM_OPERANDS and
  * MDPE_CHAIN_LAUNCH. */
 #define MDPE_SINGLE_LAUNCH 512u
+
+/* Plan flag: the kernels that workspaces of 4 GiB and more take (64-bit
+ * addresses, one term of a coefficient at a time), whatever the size; a batch
+ * with such a plan runs so too.  The same output bits; for testing them. */
+#define MDPE_WIDE_OFFSETS 2048u
 
 /* Plan summary. */
 typedef struct {

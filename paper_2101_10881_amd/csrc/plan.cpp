@@ -382,8 +382,9 @@ static double block_cost(const Plan &P, int R, int U, const LaneSchedule &ls, in
 }
 
 // The blocked kernels address the workspace by 32-bit byte offsets.
+bool small_offsets(int64_t n_series, int64_t series_doubles) { return n_series * series_doubles * 8 <= 0xffff0000LL; }
 bool small_workspace(const Plan &P) {
-    return P.n_series * (int64_t)(P.d + 1) * P.w * 8 <= 0xffff0000LL;
+    return !(P.flags & kWideOffsets) && small_offsets(P.n_series, (int64_t)(P.d + 1) * P.w);
 }
 
 // Whether reading `before` and `past` coefficients before and past the second
@@ -1474,7 +1475,7 @@ static std::string build_plan_mode(int n, int N, int d, int m, const int32_t *nv
                                    bool *unsupported) {
     *unsupported = false;
     if (flags & ~(kKeepMonomialValues | kComplex | kStreamOperands | kStageOperands | kAsapLayers | kFusedLayers |
-                  kLayerLaunches | kChainLaunch | kNoChainLaunch | kSingleLaunch))
+                  kLayerLaunches | kChainLaunch | kNoChainLaunch | kSingleLaunch | kWideOffsets))
         return "unknown flags";
     if ((flags & kChainLaunch) && (flags & (kFusedLayers | kLayerLaunches | kStreamOperands | kNoChainLaunch)))
         return "MDPE_CHAIN_LAUNCH excludes MDPE_FUSED_LAYERS, MDPE_LAYER_LAUNCHES, MDPE_STREAM_OPERANDS and "

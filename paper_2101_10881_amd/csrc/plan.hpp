@@ -86,6 +86,7 @@ constexpr uint32_t kLayerLaunches = 64u;   // one launch per convolution layer (
 constexpr uint32_t kChainLaunch = 128u;    // first-operand chains in one pipelined launch (see Plan::pipe_*)
 constexpr uint32_t kNoChainLaunch = 256u;  // never the chain launch (the plan chooses the rest)
 constexpr uint32_t kSingleLaunch = 512u;   // the whole evaluation in one launch of one workgroup
+constexpr uint32_t kWideOffsets = 2048u;   // the kernels of workspaces of 4 GiB and more, whatever the size
 
 // Chain launch: the code of an idle stretch in a lane's entry list (job field)
 constexpr int32_t kIdleJob = 0x7FFF;    // codes stay positive; chain jobs are numbered below it
@@ -255,6 +256,7 @@ long most_waves(const Plan &P);
 // Whether a launch of `waves` one-wavefront workgroups, in a plan whose largest has
 // `most`, takes one wavefront per SIMD by register count (md.hpp, one_per_simd).
 bool lone_launch(long most, long waves, int simds);
+bool small_offsets(int64_t n_series, int64_t series_doubles);
 bool small_workspace(const Plan &P);
 bool reads_inside(const Plan &P, const std::vector<std::array<int32_t, 3>> &jobs, int before, int past);
 // The rules every plan meets (Section 5: the jobs of one layer are

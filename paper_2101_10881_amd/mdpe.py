@@ -30,6 +30,7 @@ MDPE_LAYER_LAUNCHES = 64
 MDPE_CHAIN_LAUNCH = 128
 MDPE_NO_CHAIN_LAUNCH = 256
 MDPE_SINGLE_LAUNCH = 512
+MDPE_WIDE_OFFSETS = 2048
 SUPPORTED_M = (1, 2, 3, 4, 5, 8, 10)
 
 
