@@ -661,34 +661,8 @@ int launch_graph_on(mdpe_batch *b, hipStream_t stream) {
 
 }  // namespace
 
-extern "C" {
-
-int plan_batch(const mdpe_plan *const *plans, int count, const char *tune_cache, mdpe_batch **out) {
-    if (!plans || !out || count <= 0) return bfail(MDPE_EINVAL, "plans, count > 0 and out are required");
-    *out = nullptr;
-    std::vector<mdpe_batch_tile> tiles;
-    if (tune_cache && *tune_cache) {
-        if (!plans[0]) return bfail(MDPE_EINVAL, "NULL plan in the batch");
-        std::string err;
-        try {
-            err = read_tune_cache(tune_cache, device_arch(plans[0]->device), tiles);
-        } catch (const std::bad_alloc &) {
-            return bfail(MDPE_ENOMEM, "host allocation failed while reading the tune cache");
-        }
-        if (!err.empty()) return bfail(MDPE_EINVAL, err);
-    }
-    return plan_batch_tiles(plans, count, tiles.data(), (int)tiles.size(), out);
-}
-
-int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_tile *tiles, int ntiles,
-                     mdpe_batch **out) {
-    if (!plans || !out || count <= 0) return bfail(MDPE_EINVAL, "plans, count > 0 and out are required");
-    if (ntiles < 0 || (ntiles > 0 && !tiles)) return bfail(MDPE_EINVAL, "bad tiles");
-    for (int q = 0; q < ntiles; ++q)
-        if (tiles[q].deal < 0 || tiles[q].deal > 2) return bfail(MDPE_EINVAL, "a tile's deal must be 0, 1 or 2");
-    *out = nullptr;
-    std::unique_ptr<mdpe_batch> B(new (std::nothrow) mdpe_batch());
-    if (!B) return bfail(MDPE_ENOMEM, "host allocation failed");
+// The batch's queue and device arrays; on failure the caller frees it.
+static int make_batch(mdpe_batch *B, const mdpe_plan *const *plans, int count, const mdpe_batch_tile *tiles, int ntiles) {
     B->count = count;
     std::vector<int> ms;
     for (int p = 0; p < count; ++p) {
@@ -1030,10 +1004,7 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
     B->lds = lds;
     B->stage_tasks.assign(4, 0);
     for (auto &t : B->tasks) B->stage_tasks[t.kind]++;
-    if (B->device < 0) {  // host-only batch: for inspecting the queue
-        *out = B.release();
-        return MDPE_OK;
-    }
+    if (B->device < 0) return MDPE_OK;  // host-only batch: for inspecting the queue
     // device arrays
     int prev = -1;
     (void)hipGetDevice(&prev);
@@ -1090,6 +1061,43 @@ int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_
         if (e != hipSuccess) rc = bfail(MDPE_EDEVICE, std::string("pinned pointer tables: ") + hipGetErrorString(e));
     }
     if (prev >= 0) (void)hipSetDevice(prev);
+    return rc;
+}
+
+extern "C" {
+
+int plan_batch(const mdpe_plan *const *plans, int count, const char *tune_cache, mdpe_batch **out) {
+    if (!plans || !out || count <= 0) return bfail(MDPE_EINVAL, "plans, count > 0 and out are required");
+    *out = nullptr;
+    std::vector<mdpe_batch_tile> tiles;
+    if (tune_cache && *tune_cache) {
+        if (!plans[0]) return bfail(MDPE_EINVAL, "NULL plan in the batch");
+        std::string err;
+        try {
+            err = read_tune_cache(tune_cache, device_arch(plans[0]->device), tiles);
+        } catch (const std::bad_alloc &) {
+            return bfail(MDPE_ENOMEM, "host allocation failed while reading the tune cache");
+        }
+        if (!err.empty()) return bfail(MDPE_EINVAL, err);
+    }
+    return plan_batch_tiles(plans, count, tiles.data(), (int)tiles.size(), out);
+}
+
+int plan_batch_tiles(const mdpe_plan *const *plans, int count, const mdpe_batch_tile *tiles, int ntiles,
+                     mdpe_batch **out) {
+    if (!plans || !out || count <= 0) return bfail(MDPE_EINVAL, "plans, count > 0 and out are required");
+    if (ntiles < 0 || (ntiles > 0 && !tiles)) return bfail(MDPE_EINVAL, "bad tiles");
+    for (int q = 0; q < ntiles; ++q)
+        if (tiles[q].deal < 0 || tiles[q].deal > 2) return bfail(MDPE_EINVAL, "a tile's deal must be 0, 1 or 2");
+    *out = nullptr;
+    std::unique_ptr<mdpe_batch> B(new (std::nothrow) mdpe_batch());
+    if (!B) return bfail(MDPE_ENOMEM, "host allocation failed");
+    int rc;
+    try {
+        rc = make_batch(B.get(), plans, count, tiles, ntiles);
+    } catch (const std::bad_alloc &) {
+        rc = bfail(MDPE_ENOMEM, "host allocation failed while planning the batch");
+    }
     if (rc) {
         std::string keep = mdpe::get_last_error();
         free_batch(B.release());

@@ -779,6 +779,61 @@ int scratch_address(int device, void **out) {
 }
 }  // namespace
 
+// The plan's arrays on `device`; on failure the caller frees the plan.
+static int upload_plan(mdpe_plan &pl, int device) {
+    int ndev = 0;
+    HIP_TRY(hipGetDeviceCount(&ndev));
+    if (device >= ndev) return fail(MDPE_EINVAL, "no such device");
+    DeviceGuard g(device);
+    if (!g.ok) return fail(MDPE_EDEVICE, "cannot select device");
+    pl.device = device;
+    const mdpe::Plan &P = pl.P;
+    std::vector<int4> conv(P.conv.size());
+    for (size_t q = 0; q < P.conv.size(); ++q) conv[q] = make_int4(P.conv[q][0], P.conv[q][1], P.conv[q][2], 0);
+    std::vector<int4> corr(P.corr.size());
+    for (size_t q = 0; q < P.corr.size(); ++q) corr[q] = make_int4(P.corr[q][0], P.corr[q][1], P.corr[q][2], 0);
+    std::vector<int4> scale(P.scale.size());
+    for (size_t q = 0; q < P.scale.size(); ++q) scale[q] = make_int4(P.scale[q][0], P.scale[q][1], P.scale[q][2], 0);
+    std::vector<int4> fconv(P.fused_conv.size());
+    for (size_t q = 0; q < P.fused_conv.size(); ++q)
+        fconv[q] = make_int4(P.fused_conv[q][0], P.fused_conv[q][1], P.fused_conv[q][2], 0);
+    std::vector<int4> pjobs(P.pipe_jobs.size());
+    for (size_t q = 0; q < P.pipe_jobs.size(); ++q)
+        pjobs[q] = make_int4(P.pipe_jobs[q][0], P.pipe_jobs[q][1], P.pipe_jobs[q][2], 0);
+    std::vector<int32_t> coff(P.conv_off.begin(), P.conv_off.end()), aoff(P.add_off.begin(), P.add_off.end());
+    std::vector<int2> add(P.add.size()), stage(P.stage.size());
+    for (size_t q = 0; q < P.add.size(); ++q) add[q] = make_int2(P.add[q][0], P.add[q][1]);
+    for (size_t q = 0; q < P.stage.size(); ++q) stage[q] = make_int2(P.stage[q][0], P.stage[q][1]);
+    const mdpe::AddPasses passes = mdpe::make_add_passes(P, mdpe::add_pass_leaves(P.w));
+    pl.add_pass = passes.off;
+    mdpe_plan *raw = &pl;
+    Arena arena;
+    arena.add(&raw->d_conv, conv.data(), conv.size() * sizeof(int4));
+    arena.add(&raw->d_add, add.data(), add.size() * sizeof(int2));
+    arena.add(&raw->d_stage, stage.data(), stage.size() * sizeof(int2));
+    arena.add(&raw->d_out, P.out_slots.data(), P.out_slots.size() * sizeof(int));
+    arena.add(&raw->d_chains, P.lanes.chains.data(), P.lanes.chains.size() * sizeof(int));
+    arena.add(&raw->d_corr, corr.data(), corr.size() * sizeof(int4));
+    arena.add(&raw->d_cbar, P.coeff_bar_slots.data(), P.coeff_bar_slots.size() * sizeof(int));
+    arena.add(&raw->d_zbar, P.z_bar_slots.data(), P.z_bar_slots.size() * sizeof(int));
+    arena.add(&raw->d_ybar, &P.ybar_slot, sizeof(int));
+    arena.add(&raw->d_scale, scale.data(), scale.size() * sizeof(int4));
+    arena.add(&raw->d_fconv, fconv.data(), fconv.size() * sizeof(int4));
+    arena.add(&raw->d_foff, P.fused_off.data(), P.fused_off.size() * sizeof(int));
+    arena.add(&raw->d_fchains, P.fused_lanes.chains.data(), P.fused_lanes.chains.size() * sizeof(int));
+    arena.add(&raw->d_pjobs, pjobs.data(), pjobs.size() * sizeof(int4));
+    arena.add(&raw->d_pcomps, P.pipe_comps.data(), P.pipe_comps.size() * sizeof(mdpe::ChainComp));
+    arena.add(&raw->d_pcodes, P.pipe_codes.data(), P.pipe_codes.size() * sizeof(int));
+    arena.add(&raw->d_blocks, P.blocks.chains.data(), P.blocks.chains.size() * sizeof(int));
+    arena.add(&raw->d_fblocks, P.fused_blocks.chains.data(), P.fused_blocks.chains.size() * sizeof(int));
+    arena.add(&raw->d_leaves, passes.leaves.data(), passes.leaves.size() * sizeof(int));
+    arena.add(&raw->d_chunks, passes.chunks.data(), passes.chunks.size() * sizeof(mdpe::AddChunk));
+    arena.add(&raw->d_coff, coff.data(), coff.size() * sizeof(int));
+    arena.add(&raw->d_aoff, aoff.data(), aoff.size() * sizeof(int));
+    arena.add(&raw->d_schains, P.single_lanes.chains.data(), P.single_lanes.chains.size() * sizeof(int));
+    return arena.upload(&raw->d_arena);
+}
+
 extern "C" {
 
 int plan_polynomial(const mdpe_poly_desc *desc, int device, mdpe_plan **out) {
@@ -801,64 +856,19 @@ int plan_polynomial(const mdpe_poly_desc *desc, int device, mdpe_plan **out) {
     }
     if (!err.empty()) return fail(unsupported ? MDPE_EUNSUPPORTED : MDPE_EINVAL, err);
     pl->most_waves = mdpe::most_waves(pl->P);
+    int rc = MDPE_OK;
     if (device >= 0) {
-        int ndev = 0;
-        HIP_TRY(hipGetDeviceCount(&ndev));
-        if (device >= ndev) return fail(MDPE_EINVAL, "no such device");
-        DeviceGuard g(device);
-        if (!g.ok) return fail(MDPE_EDEVICE, "cannot select device");
-        pl->device = device;
-        const mdpe::Plan &P = pl->P;
-        std::vector<int4> conv(P.conv.size());
-        for (size_t q = 0; q < P.conv.size(); ++q) conv[q] = make_int4(P.conv[q][0], P.conv[q][1], P.conv[q][2], 0);
-        std::vector<int4> corr(P.corr.size());
-        for (size_t q = 0; q < P.corr.size(); ++q) corr[q] = make_int4(P.corr[q][0], P.corr[q][1], P.corr[q][2], 0);
-        std::vector<int4> scale(P.scale.size());
-        for (size_t q = 0; q < P.scale.size(); ++q) scale[q] = make_int4(P.scale[q][0], P.scale[q][1], P.scale[q][2], 0);
-        std::vector<int4> fconv(P.fused_conv.size());
-        for (size_t q = 0; q < P.fused_conv.size(); ++q)
-            fconv[q] = make_int4(P.fused_conv[q][0], P.fused_conv[q][1], P.fused_conv[q][2], 0);
-        std::vector<int4> pjobs(P.pipe_jobs.size());
-        for (size_t q = 0; q < P.pipe_jobs.size(); ++q)
-            pjobs[q] = make_int4(P.pipe_jobs[q][0], P.pipe_jobs[q][1], P.pipe_jobs[q][2], 0);
-        std::vector<int32_t> coff(P.conv_off.begin(), P.conv_off.end()), aoff(P.add_off.begin(), P.add_off.end());
-        std::vector<int2> add(P.add.size()), stage(P.stage.size());
-        for (size_t q = 0; q < P.add.size(); ++q) add[q] = make_int2(P.add[q][0], P.add[q][1]);
-        for (size_t q = 0; q < P.stage.size(); ++q) stage[q] = make_int2(P.stage[q][0], P.stage[q][1]);
-        const mdpe::AddPasses passes = mdpe::make_add_passes(P, mdpe::add_pass_leaves(P.w));
-        pl->add_pass = passes.off;
-        int rc;
-        mdpe_plan *raw = pl.get();
-        Arena arena;
-        arena.add(&raw->d_conv, conv.data(), conv.size() * sizeof(int4));
-        arena.add(&raw->d_add, add.data(), add.size() * sizeof(int2));
-        arena.add(&raw->d_stage, stage.data(), stage.size() * sizeof(int2));
-        arena.add(&raw->d_out, P.out_slots.data(), P.out_slots.size() * sizeof(int));
-        arena.add(&raw->d_chains, P.lanes.chains.data(), P.lanes.chains.size() * sizeof(int));
-        arena.add(&raw->d_corr, corr.data(), corr.size() * sizeof(int4));
-        arena.add(&raw->d_cbar, P.coeff_bar_slots.data(), P.coeff_bar_slots.size() * sizeof(int));
-        arena.add(&raw->d_zbar, P.z_bar_slots.data(), P.z_bar_slots.size() * sizeof(int));
-        arena.add(&raw->d_ybar, &P.ybar_slot, sizeof(int));
-        arena.add(&raw->d_scale, scale.data(), scale.size() * sizeof(int4));
-        arena.add(&raw->d_fconv, fconv.data(), fconv.size() * sizeof(int4));
-        arena.add(&raw->d_foff, P.fused_off.data(), P.fused_off.size() * sizeof(int));
-        arena.add(&raw->d_fchains, P.fused_lanes.chains.data(), P.fused_lanes.chains.size() * sizeof(int));
-        arena.add(&raw->d_pjobs, pjobs.data(), pjobs.size() * sizeof(int4));
-        arena.add(&raw->d_pcomps, P.pipe_comps.data(), P.pipe_comps.size() * sizeof(mdpe::ChainComp));
-        arena.add(&raw->d_pcodes, P.pipe_codes.data(), P.pipe_codes.size() * sizeof(int));
-        arena.add(&raw->d_blocks, P.blocks.chains.data(), P.blocks.chains.size() * sizeof(int));
-        arena.add(&raw->d_fblocks, P.fused_blocks.chains.data(), P.fused_blocks.chains.size() * sizeof(int));
-        arena.add(&raw->d_leaves, passes.leaves.data(), passes.leaves.size() * sizeof(int));
-        arena.add(&raw->d_chunks, passes.chunks.data(), passes.chunks.size() * sizeof(mdpe::AddChunk));
-        arena.add(&raw->d_coff, coff.data(), coff.size() * sizeof(int));
-        arena.add(&raw->d_aoff, aoff.data(), aoff.size() * sizeof(int));
-        arena.add(&raw->d_schains, P.single_lanes.chains.data(), P.single_lanes.chains.size() * sizeof(int));
-        if ((rc = arena.upload(&raw->d_arena))) {
-            std::string keep = g_err;
-            free_plan(pl.release());
-            g_err = keep;
-            return rc;
+        try {
+            rc = upload_plan(*pl, device);
+        } catch (const std::bad_alloc &) {
+            rc = fail(MDPE_ENOMEM, "host allocation failed while uploading the plan");
         }
+    }
+    if (rc) {
+        std::string keep = g_err;
+        free_plan(pl.release());
+        g_err = keep;
+        return rc;
     }
     *out = pl.release();
     return MDPE_OK;
