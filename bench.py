@@ -706,7 +706,7 @@ def main():
         "config": {"workload": w.name, "polynomial": "p1: all 1820 products of 4 of 16 variables",
                    "m": m, "d": d, "n": w.n, "N": w.N, "seed": 1,
                    "n_conv": info["n_conv"], "n_add": info["n_add"],
-                   "conv_launches": [int(x) for x in conv_sizes], "add_launches": [int(x) for x in add_sizes]},
+                   "conv_launches": [int(x) for x in conv_sizes], "add_levels": [int(x) for x in add_sizes]},
         "roofline": {
             "kernel": "conv_layer_kernel<10>",
             "bound": "alu",

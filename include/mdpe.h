@@ -383,7 +383,9 @@ int plan_reverse_jobs(const mdpe_plan *plan, int32_t *rows);
 
 /* Per-kernel timing with HIP events recorded on the launch stream, in the
  * paper's four categories (Section 6.2: convolution, addition, their sum; the
- * caller measures wall time).  Times accumulate over calls until read. */
+ * caller measures wall time).  The last addition pass writes value and gradient:
+ * its time is the additions', and the gather's is nothing, unless the polynomial
+ * has no additions.  Times accumulate over calls until read. */
 typedef struct mdpe_profiler mdpe_profiler;
 typedef struct {
     double stage_ms, cnv_ms, add_ms, gather_ms;

@@ -5,8 +5,10 @@ A tile, per (m, d) bucket, is
     jobs_per_group     convolution jobs per wavefront pass (lane schedule)
     groups_per_task    passes per convolution task
     add_items_per_task coefficients per addition / staging / gather task
-    deal               at two doubles: the cost model's choice (0), the lane
-                       schedule (1) or coefficients dealt to lanes in turn (2)
+    deal               at one double: the cost model's choice (0), the lane
+                       schedule (1) or coefficients dealt to lanes in turn (2);
+                       from two doubles on convolutions run by blocks, which
+                       have one order
 
 The tiles of all buckets interact: the persistent kernel's LDS size, hence
 its occupancy, is the maximum over instances, and every bucket's tasks share
@@ -43,7 +45,7 @@ def default_jobs_per_group(d: int) -> int:
 def candidates(m: int, d: int):
     J0 = default_jobs_per_group(d)
     js = sorted({J0, max(1, J0 // 2), min(64, 2 * J0)})
-    deals = [0, 1, 2] if m <= 2 else [0]
+    deals = [0, 1, 2] if m == 1 else [0]
     for J, G, A, D in itertools.product(js, [1, 2, 4, 8, 16], [1024, 4096, 16384], deals):
         yield {"m": m, "d": d, "jobs_per_group": J, "groups_per_task": G, "add_items_per_task": A, "deal": D}
 
@@ -51,7 +53,7 @@ def candidates(m: int, d: int):
 def neighbours(m: int, d: int, tile: dict):
     """Tiles one field away from `tile` (the default tile's fields where it has none): jobs per
     group and groups per task by factors 1/2, 2/3, 3/4, 4/3, 3/2 and 2, addition items halved
-    or doubled, and the other coefficient orders at two doubles."""
+    or doubled, and the other coefficient orders at one double."""
     base = {"m": m, "d": d, "jobs_per_group": tile.get("jobs_per_group") or default_jobs_per_group(d),
             "groups_per_task": tile.get("groups_per_task") or 0, "add_items_per_task": tile.get("add_items_per_task") or 4096,
             "deal": tile.get("deal", 0)}
@@ -69,7 +71,7 @@ def neighbours(m: int, d: int, tile: dict):
     for A in (base["add_items_per_task"] // 2, base["add_items_per_task"] * 2):
         if A >= 256:
             yield from out({**base, "add_items_per_task": A})
-    if m <= 2:
+    if m == 1:
         for D in (0, 1, 2):
             yield from out({**base, "deal": D})
 

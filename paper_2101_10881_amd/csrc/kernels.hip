@@ -679,14 +679,14 @@ int eval_impl(const mdpe_plan *pl, const double *coeff, const double *z, double 
         default: return fail(MDPE_EUNSUPPORTED, "unsupported m");
     }
     if (rc) return rc;
-    // the addition trees; the last pass writes value and gradient
-    const int passes = (int)pl->add_pass.size() - 1;
-    for (int p = 0; p < passes; ++p) {
-        const int cls = p + 1 < passes ? 2 : 3;
+    // the addition trees; the last pass writes value and gradient.  Timed as
+    // additions, the gather then as nothing; without additions as the gather.
+    const int passes = (int)pl->add_pass.size() - 1, cls = P.add.empty() ? 3 : 2;
+    for (int p = 0; p < passes; ++p)
         if ((rc = record(prof, cls, st, true)) || (rc = mdpe::launch_add_pass(pl, p, A, value, grad, st)) ||
             (rc = record(prof, cls, st, false)))
             return rc;
-    }
+    if (cls == 2 && ((rc = record(prof, 3, st, true)) || (rc = record(prof, 3, st, false)))) return rc;
     return MDPE_OK;
 }
 
