@@ -27,6 +27,7 @@
 #include "plan.hpp"
 
 #include <cmath>
+#include <limits>
 
 #include <algorithm>
 #include <numeric>
@@ -437,7 +438,11 @@ long most_waves(const Plan &P) {
     for (int L = P.pipe_layers + 1; L <= P.n_layers(); ++L)
         most = std::max<long>(most, (P.conv_off[L] - P.conv_off[L - 1] + ls.jobs_per_group - 1) / ls.jobs_per_group *
                                         (long)ls.waves_per_job);
-    return most;
+    return most_after_chains(most, P.pipe_layers > 0 ? P.pipe_waves : 0);
+}
+
+long most_after_chains(long largest, int chain_waves) {
+    return chain_waves >= 2 ? std::numeric_limits<long>::max() : largest;
 }
 
 // A plan's launches all do or none does: a launch without it goes on from wherever
@@ -447,6 +452,12 @@ long most_waves(const Plan &P) {
 //   variables, ten doubles, d = 31: the first layer, 910 wavefronts, 160 us with it
 //   and 278 without; five doubles, d = 63: the last one 58 and 92).  Two streams
 //   gain too (eight doubles, d = 95: 5044 and 5450 us for two evaluations).
+// - So does a chain launch of two wavefronts or more per chain for the layers behind
+//   it (100 chains of 16, five doubles, d = 20, two wavefronts: 84 us with it and 95
+//   without, two streams 108 and 121; 183 of 12, three doubles, d = 27, 56 and 60, 71
+//   and 77; 29 of 24, five doubles, d = 57, four wavefronts, two streams 295 and
+//   339).  One wavefront per chain leaves them even (13 plans, 1.00), and two
+//   streams lose (317 of 17, ten doubles, d = 8: 408 us without it, 536 with).
 // - Up to a round the placement is even without it (20 workloads, 0.99 to 1.01 of
 //   the time), and it would keep two streams' launches from sharing SIMDs: two
 //   evaluations with it and without, 330 products of four of eleven variables at

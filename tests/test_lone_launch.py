@@ -28,3 +28,15 @@ def _lone(most, waves, simds):
 ])
 def test_lone_launch(most, waves, want):
     assert _lone(most, waves, 1024) is want
+
+
+@pytest.mark.parametrize("chain_waves,want", [(0, False), (1, False), (2, True), (4, True), (16, True)])
+def test_lone_launch_behind_chains(chain_waves, want):
+    """A layer of up to a round takes it behind chains of two wavefronts or more, whose
+    workgroups leave the SIMDs uneven, and not behind chains of one."""
+    f = getattr(mdpe.lib(), "_ZN4mdpe17most_after_chainsEli")  # mdpe::most_after_chains(long, int)
+    f.argtypes, f.restype = [ctypes.c_long, ctypes.c_int], ctypes.c_long
+    assert f(700, 0) == 700
+    assert _lone(f(700, chain_waves), 700, 1024) is want
+    assert not _lone(f(700, chain_waves), 256, 1024)
+    assert not _lone(f(700, chain_waves), 1025, 1024)
