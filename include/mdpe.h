@@ -138,10 +138,13 @@ typedef struct {
 #define MDPE_LAYER_LAUNCHES 64u
 
 /* Plan flag: run the chains of products in one pipelined launch (plans do so
- * by themselves where it is estimated well under the layered or fused
- * launches: chains of at least 16 products holding a quarter of the
- * convolutions or more, such as p2's).  A chain is a sequence of
- * convolutions where each job's first operand is the previous job's output
+ * by themselves where it is estimated under 0.9 of the layered launches and, at
+ * one double per coefficient, under the fused one: chains of at least nine
+ * products -- 16 when there are fewer than 64 chains -- holding a quarter of the
+ * convolutions or more, at one double up to d = 190.  A plan whose workspace
+ * stays within eval_and_diff_noalloc's without it keeps it there, except for
+ * chains of 16 products or more that save a tenth by a stricter estimate).
+ * A chain is a sequence of convolutions where each job's first operand is the previous job's output
  * and its second a staged input series: the forward products f_j = f_{j-1} *
  * z_{i_j} and the backward products b_j = b_{j-1} * z_{i_{n-j}} of Section 3.
  * Coefficient i of a product is final once its own i+1 terms are summed, and
@@ -161,9 +164,9 @@ typedef struct {
 #define MDPE_NO_CHAIN_LAUNCH 256u
 
 /* Plan flag: the whole evaluation in one launch of one workgroup (plans do so
- * by themselves where it is estimated under 0.7 of the per-launch time: plans
- * so small that the boundaries between their ~10 dependent launches, ~4.5 us
- * each on MI355X, dominate, such as 16 three-variable monomials at d = 8).
+ * by themselves where it is estimated faster than staging, a launch per layer and
+ * the addition passes: plans so small that the boundaries between those launches
+ * dominate, such as 16 three-variable monomials at d = 8).
  * The workgroup's wavefronts run staging, every convolution layer (each
  * wavefront a group of jobs per round, as in a per-layer launch), the scale
  * stage, every addition level and the gather, with a workgroup barrier after
@@ -183,7 +186,7 @@ typedef struct {
     int64_t n_conv;         /* convolution jobs: sum over monomials of 3 n_k - 3 (1 if n_k = 1) */
     int64_t n_add;          /* addition jobs */
     int32_t n_layers;       /* convolution launches = largest n_k */
-    int32_t n_levels;       /* addition launches */
+    int32_t n_levels;       /* levels of the addition trees */
     int64_t workspace_bytes;/* device workspace eval_and_diff needs: n_series*(d+1)*m*8, twice that
                                for MDPE_COMPLEX */
     int32_t jobs_per_group; /* convolution jobs per 64-lane workgroup */
@@ -226,7 +229,7 @@ int plan_polynomial(const mdpe_poly_desc *desc, int device, mdpe_plan **out);
 
 int plan_info(const mdpe_plan *plan, mdpe_plan_info *out);
 
-/* conv_sizes[n_layers], add_sizes[n_levels]: jobs per launch (either may be NULL). */
+/* conv_sizes[n_layers], add_sizes[n_levels]: jobs per layer and level (either may be NULL). */
 int plan_layer_sizes(const mdpe_plan *plan, int32_t *conv_sizes, int32_t *add_sizes);
 
 /* Convolution jobs as rows {layer (1-based), t1, t2, t3} in slot units (a slot
@@ -333,9 +336,13 @@ int check_plan_jobs(int32_t n, int32_t N, int64_t n_series, const int32_t *conv_
  * (plan_info): one kernel per layer, one fused launch of every layer
  * (fused_components > 0), or the chain launch followed by one kernel per
  * remaining layer (chain_layers > 0); one scale kernel when an exponent exceeds
- * one; one addition kernel per level; one gather kernel.  A plan with
- * single_launch = 1 runs all of it in one kernel.  Calls on different streams
- * must not share a workspace.
+ * one; the addition trees in passes of up to 128 leaves each (64 beyond eight
+ * doubles), one or two of them up to 16384, the last of which writes value and
+ * gradient.  A plan with single_launch = 1 runs all of it in one kernel.  Calls on
+ * different streams must not share a workspace; their kernels run side by side, but
+ * the launches of up to one wavefront per SIMD hold their SIMDs alone in plans that
+ * also have larger ones, in plans of at most half as many, and behind a chain
+ * launch of two wavefronts or more per chain.
  */
 int eval_and_diff(const mdpe_plan *plan, const double *coeff, const double *z, double *value,
                   double *grad, void *workspace, void *stream);
@@ -401,7 +408,7 @@ int eval_adjoint_profiled(const mdpe_plan *plan, const double *ybar, void *works
                           double *coeff_bar, double *z_bar, void *stream, mdpe_profiler *prof);
 /* Which launches get an event pair: a mask of MDPE_TIME_STAGE, MDPE_TIME_CONV,
  * MDPE_TIME_ADD and MDPE_TIME_GATHER (all by default).  Each pair is two more
- * commands on the stream (~0.12 ms per p1 evaluation for all 17 launches), so
+ * commands on the stream (~7 us each), so
  * a caller that needs only the convolution launches' durations times just those.
  * MDPE_EINVAL for unknown bits, or while recorded events are unread. */
 #define MDPE_TIME_STAGE 1u
@@ -446,10 +453,12 @@ typedef struct {
     int32_t m, d;
     int32_t jobs_per_group;     /* convolution jobs per wavefront pass (lane schedule) */
     int32_t groups_per_task;    /* passes per convolution task */
-    int32_t add_items_per_task; /* coefficients per addition / staging / gather task */
-    int32_t deal;               /* coefficients of at most two doubles: 0 the cost model's choice,
-                                   1 the lane schedule, 2 dealt to the lanes in turn (either gives
-                                   the same bits); ignored from three doubles on */
+    int32_t add_items_per_task; /* coefficients per staging / gather task, additions of coefficients
+                                   per addition task */
+    int32_t deal;               /* coefficients of at most two doubles, where the batch does not run
+                                   them by blocks (one double; two on workspaces of 4 GiB): 0 the
+                                   cost model's choice, 1 the lane schedule, 2 dealt to the lanes
+                                   in turn (either gives the same bits); else ignored */
 } mdpe_batch_tile;
 
 typedef struct {

@@ -21,9 +21,10 @@ constexpr int kAddRuns = kAddThreads / kAddCoefs;    // runs of leaves of a work
 // the tree's own pairs (later element + earlier one, an odd one carried), so
 // every sum is that of the level-by-level additions.  Bound by the latency of
 // a pass at these sizes: one launch per level (each ~4.7 us, bound by its
-// boundary) took 35-77 us for 8 to 13 levels, a pass takes 4 to 13 us.  Each
-// leaf is read once and each part written once, where a launch per level
-// reads two series and writes one per addition.
+// boundary) took 35-77 us for 8 to 13 levels, a pass takes 4 to 13 us (38 at ten
+// doubles, d = 152 and 1821 leaves).  Each leaf is read once and each part
+// written once, where a launch per level reads two series and writes one per
+// addition.
 template <int M, bool CX>
 __global__ __launch_bounds__(kAddThreads) void add_tree_kernel(double *__restrict__ A, const int *__restrict__ leaves,
                                                                const AddChunk *__restrict__ chunks, long parts,

@@ -777,7 +777,12 @@ static void unfuse(Plan &P) {
 // 1.17x at d = 15, 1.0x at d = 31; ten doubles 1.14x at d = 15, 1.05x at
 // d = 31; eight doubles 1.2x at d = 8 but 0.99x at d = 15 and 0.89x at d = 31
 // (the other widths take eight doubles' limit).  The caller also requires
-// every component's layer to fit one round of four wavefronts.
+// every component's layer to fit one round of four wavefronts.  By blocks and with
+// addition passes on both sides 147 of 167 random plans of 4 to 8 layers still take
+// the faster one within 6%; the line is off where layers run blocks and the fused
+// launch does not (eight and ten doubles up to d = 16: 1.08 to 1.15 times as slow
+// fused) and at layers of more than 512 short products (three to five doubles, d = 2
+// to 8: up to 1.44 by layers).
 static bool fuse_by_default(const Plan &P) {
     if (P.streamed || P.lanes.waves_per_job != 1 || P.n_layers() < 4) return false;
     if (P.w == 1 || (P.w == 2 && P.d <= 63)) return true;
@@ -1158,11 +1163,13 @@ static double chain_cost(const Plan &P, size_t chains, int R, int U, int W, int 
 // over R coefficients per block, W wavefronts per chain, a barrier every S
 // iterations and the LDS of a chain, applied when forced or estimated under 0.9
 // of `other` (the cycles of the plan without it).  Returns whether P now holds
-// a chain launch.  Chains from nine products on: shorter ones (p1's four, the
-// batched instances' at most eight) have too few layers to save; below 16
-// products from 64 chains on (211 monomials of 1 to 12 variables, five doubles,
-// d = 37: 404 -> 130 us): plans of a few short chains keep their layers and
-// their series count.
+// a chain launch.  Chains from nine products on, below 16 products from 64 chains
+// on (211 monomials of 1 to 12 variables, five doubles, d = 37: 404 -> 130 us): other
+// plans keep their layers, their workspace and their build time, not because the
+// launch would lose (5, 7, 9 and 12 products against the default, 4 to 128 chains: one
+// double, d = 16, 0.83 to 0.97, 1.01 to 1.08, 1.08 to 1.15, 1.14 to 1.25 times as fast;
+// two, d = 16, 1.1, 1.3, 1.5, 1.7; four, d = 16, 1.5, 1.9, 2.2, 2.6; eight, d = 64, 2.3,
+// 2.7, 3.0, 3.6).
 static bool choose_chain_launch(Plan &P, bool forced, double other) {
     if (P.streamed) return false;
     std::vector<std::vector<int64_t>> chains;
@@ -1402,8 +1409,10 @@ static std::string build_plan_launches(int n, int N, int d, int m, const int32_t
     // the in-place products fresh output slots: a chain's products overlap,
     // so b_{n-2} must stay readable while b_{n-2} * a_k is stored.
     const bool chain_forced = (flags & kChainLaunch) != 0;
-    // (a chain of nine products takes a monomial of at least seven variables, or
-    // a power table that long: no second plan is built for less)
+    // (no second plan is built for less than a monomial of seven variables or a power
+    // table of nine: a multilinear chain of nine products takes that much.  Monomials
+    // of five or six variables reach it through common factors, with exponents on
+    // nearly all of them, and keep their layers)
     int longest = 0;
     int64_t at = 0;
     for (int k = 0; k < N; ++k) {
