@@ -341,8 +341,8 @@ int check_plan_jobs(int32_t n, int32_t N, int64_t n_series, const int32_t *conv_
  * gradient.  A plan with single_launch = 1 runs all of it in one kernel.  Calls on
  * different streams must not share a workspace; their kernels run side by side, but
  * the launches of up to one wavefront per SIMD hold their SIMDs alone in plans that
- * also have larger ones, in plans of at most half as many, and behind a chain
- * launch of two wavefronts or more per chain.
+ * also have larger ones, in plans of at most half as many, from eight doubles on,
+ * and behind a chain launch of two wavefronts or more per chain.
  */
 int eval_and_diff(const mdpe_plan *plan, const double *coeff, const double *z, double *value,
                   double *grad, void *workspace, void *stream);

@@ -438,8 +438,11 @@ long most_waves(const Plan &P) {
     for (int L = P.pipe_layers + 1; L <= P.n_layers(); ++L)
         most = std::max<long>(most, (P.conv_off[L] - P.conv_off[L - 1] + ls.jobs_per_group - 1) / ls.jobs_per_group *
                                         (long)ls.waves_per_job);
-    return most_after_chains(most, P.pipe_layers > 0 ? P.pipe_waves : 0);
+    if (P.pipe_layers > 0) return most_after_chains(most, P.pipe_waves);
+    return lone_at(P.w) ? std::numeric_limits<long>::max() : most;
 }
+
+bool lone_at(int w) { return w >= 8; }
 
 long most_after_chains(long largest, int chain_waves) {
     return chain_waves >= 2 ? std::numeric_limits<long>::max() : largest;
@@ -458,11 +461,15 @@ long most_after_chains(long largest, int chain_waves) {
 //   and 77; 29 of 24, five doubles, d = 57, four wavefronts, two streams 295 and
 //   339).  One wavefront per chain leaves them even (13 plans, 1.00), and two
 //   streams lose (317 of 17, ten doubles, d = 8: 408 us without it, 536 with).
-// - Up to a round the placement is even without it (20 workloads, 0.99 to 1.01 of
-//   the time), and it would keep two streams' launches from sharing SIMDs: two
+// - From eight doubles on the placement within a round is not always even either
+//   (817 monomials of one to four variables, eight doubles, d = 87: 1127 us with it
+//   and 1350 without; ten, d = 141, 411 of two or three: 1970 and 2537; 10 plans
+//   1.00), and two streams gain (13 plans, 0.83 to 1.05 of the time, 0.92 together).
+// - Below eight doubles it is even up to a round (45 workloads, 0.99 to 1.01 of the
+//   time), and it would keep two streams' launches from sharing SIMDs: two
 //   evaluations with it and without, 330 products of four of eleven variables at
-//   five doubles, d = 63, 342 and 302 us, at four, d = 95, 307 and 267; 495 of
-//   twelve at eight, d = 40, 633 and 584.
+//   five doubles, d = 63, 342 and 302 us, at four, d = 95, 307 and 267; 631 of two
+//   to six variables at two, d = 76, 129 and 100.
 // - Up to half a round two streams' launches fit beside each other, and it puts
 //   them there: eight and ten doubles, launches of 210 to 495, 0.77 to 0.96 of the
 //   time of two streams without it.

@@ -251,8 +251,10 @@ bool earliest_layers(const Plan &P, std::vector<std::array<int32_t, 3>> &conv, s
 // job's second operand lie inside it.
 int block_terms_of(int w, int d);
 // Wavefronts of the largest convolution launch of a plan run layer by layer (0:
-// none is); more than any round behind a chain launch that leaves the SIMDs uneven.
+// none is); more than any round where the SIMDs are uneven anyway: from eight doubles
+// per coefficient on, and behind a chain launch that leaves them so.
 long most_waves(const Plan &P);
+bool lone_at(int w);
 long most_after_chains(long largest, int chain_waves);
 // Whether a launch of `waves` one-wavefront workgroups, in a plan whose largest has
 // `most`, takes one wavefront per SIMD by register count (md.hpp, one_per_simd).

@@ -40,3 +40,11 @@ def test_lone_launch_behind_chains(chain_waves, want):
     assert _lone(f(700, chain_waves), 700, 1024) is want
     assert not _lone(f(700, chain_waves), 256, 1024)
     assert not _lone(f(700, chain_waves), 1025, 1024)
+
+
+@pytest.mark.parametrize("w,want", [(1, False), (4, False), (5, False), (8, True), (10, True), (20, True)])
+def test_lone_launch_of_wide_coefficients(w, want):
+    """From eight doubles on every launch of a quarter round to a round takes it."""
+    f = getattr(mdpe.lib(), "_ZN4mdpe7lone_atEi")  # mdpe::lone_at(int)
+    f.argtypes, f.restype = [ctypes.c_int], ctypes.c_bool
+    assert f(w) is want
