@@ -166,7 +166,9 @@ typedef struct {
 /* Plan flag: the whole evaluation in one launch of one workgroup (plans do so
  * by themselves where it is estimated faster than staging, a launch per layer and
  * the addition passes: plans so small that the boundaries between those launches
- * dominate, such as 16 three-variable monomials at d = 8).
+ * dominate, such as 16 three-variable monomials at d = 8; with
+ * MDPE_KEEP_MONOMIAL_VALUES also up to an estimated 40 us, which the host's work
+ * for both passes hides).
  * The workgroup's wavefronts run staging, every convolution layer (each
  * wavefront a group of jobs per round, as in a per-layer launch), the scale
  * stage, every addition level and the gather, with a workgroup barrier after

@@ -1388,14 +1388,20 @@ static SingleCost single_launch_cost(const Plan &P) {
     return c;
 }
 
-static bool choose_single_launch(Plan &P, bool forced) {
+static bool choose_single_launch(Plan &P, bool forced, bool keep) {
     if (P.streamed || P.pipe_layers > 0 || P.fused_components > 0) return false;
     const SingleCost c = single_launch_cost(P);
     // (of 230 plans measured both ways the choice takes 1.02 times the better one's time
     // together; below 17 us, where launches alone tie the estimates, one workgroup
     // keeps the plans up to 1.4: 78 monomials of one or two variables, two doubles, d =
-    // 3, 13.1 us and 16.0 by layers)
-    const double most = c.multi_us < 17.0 ? 1.4 * c.multi_us : c.multi_us;
+    // 3, 13.1 us and 16.0 by layers).  A plan that keeps the monomial values serves
+    // autograd, whose host work for both passes (57 to 115 us) hides some 40 us of one
+    // workgroup's evaluation and the reverse pass behind it, and is shorter by three
+    // launches or more (55 plans, 0.84 to 0.93 of the time by layers up to 40 us; 120
+    // products of two of sixteen variables, one double, d = 15, 107 and 122 us, the
+    // evaluation alone 19 and 14)
+    double most = c.multi_us < 17.0 ? 1.4 * c.multi_us : c.multi_us;
+    if (keep) most = std::max(most, 40.0);
     if (c.single_us < 0 || (!forced && c.single_us >= most)) return false;
     P.single = true;
     P.single_waves = c.waves;
@@ -1489,7 +1495,7 @@ std::string build_plan(int n, int N, int d, int m, const int32_t *nvars, const i
     if (!err.empty()) return err;
     P.flags = flags;
     if (forced || !(flags & (kLayerLaunches | kFusedLayers | kChainLaunch | kStreamOperands))) {
-        if (!choose_single_launch(P, forced) && forced) {
+        if (!choose_single_launch(P, forced, (flags & kKeepMonomialValues) != 0) && forced) {
             *unsupported = true;
             return "MDPE_SINGLE_LAUNCH: a job group does not fit in the workgroup's LDS";
         }

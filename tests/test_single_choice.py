@@ -25,3 +25,20 @@ def test_many_additions_or_long_products_take_a_launch_per_layer(args):
                                   (8, 16, 3, 3, 2, 8)])
 def test_the_smallest_take_one_workgroup(args):
     assert _single(*args)
+
+
+def _kept(n, r, m, d, flags):
+    return mdpe.Plan.for_workload(W.make("s", m, d, n, W.all_subsets(n, r), seed=1), device=-1,
+                                  flags=flags).info["single_launch"]
+
+
+# through autograd 107 and 122, 113 and 122, 114 and 122 us, alone 19 and 14, 24 and 15, 22 and 15
+@pytest.mark.parametrize("args", [(16, 2, 1, 15), (15, 2, 1, 14), (13, 2, 2, 6)])
+def test_a_plan_with_a_reverse_pass_takes_one_workgroup_for_fewer_launches(args):
+    assert _kept(*args, mdpe.MDPE_KEEP_MONOMIAL_VALUES) and not _kept(*args, 0)
+
+
+# 86 and 43, 119 and 38, 124 and 45 with the reverse pass
+@pytest.mark.parametrize("args", [(8, 3, 2, 12), (10, 2, 2, 31), (14, 3, 1, 13)])
+def test_but_not_where_the_device_is_what_takes_time(args):
+    assert not _kept(*args, mdpe.MDPE_KEEP_MONOMIAL_VALUES)
